@@ -203,10 +203,10 @@ int score_impl(avtp_stream_t stream, const avtp_layout *layout, int mode, int dt
   float *lse2 = (float *)(w + P.off_lse2);  // row LSE in log2 units, for pass 2
   if (L.T_tot > 0) {
     if (row_lse)
-      e = launch_lse_to_log2(st, Hq * L.T_tot, row_lse, lse2);
+      e = launch_lse_to_log2(st, L.T_tot, Hq, row_lse, lse2);
     else
       e = launch_row_lse(st, L, P, dtype, q_text, k, Hq, Hkv, d, softmax_scale,
-                         (float *)(w + P.off_lse), lse2, w);
+                         nullptr, lse2, w);
   }
   if (e == hipSuccess && L.T_tot > 0)
     e = launch_colsum(st, L, P, dtype, q_text, k, Hq, Hkv, d, softmax_scale, lse2, w);

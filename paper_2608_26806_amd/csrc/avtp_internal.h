@@ -33,6 +33,7 @@ struct AttnPlan {
   int rows_max;   // max over sequences of G * T_b
   int nqb;        // query blocks per (sequence, key head) in pass 1
   int nt1;        // 32-row query tiles per wave in pass 1
+  bool small1;    // pass 1 of fp32 inputs in its small-grid form
   int kchunk;     // keys per pass-1 chunk (multiple of 64)
   int nkc;        // chunks per sequence (max)
   int nkb;        // key blocks per (sequence, key head) in pass 2
@@ -40,7 +41,7 @@ struct AttnPlan {
   int nqs;        // query splits of pass 2 (column-sum planes per key head)
   int nsl;        // pass 2: each (sequence, key head)'s key blocks are dealt to nsl
                   // slices (kb mod nsl), so that there are units for all 8 XCDs
-  size_t off_part_m, off_part_l, off_lse, off_lse2, off_colsum, bytes;
+  size_t off_part_m, off_part_l, off_lse2, off_colsum, bytes;
 };
 
 AttnPlan attn_plan(const DevLayout &L, int Hq, int Hkv, int d, int dtype);
@@ -55,13 +56,13 @@ int score_impl(avtp_stream_t stream, const avtp_layout *layout, int mode, int dt
                size_t *ws_need);
 size_t variation_workspace_bytes(const DevLayout &L);
 
-// Pass 1 and the combine: the row LSE (natural log) into row_lse and, if
-// lse2 is not null, in log2 units into lse2.
+// Pass 1 and the combine: the row LSE (natural log, [Hq][T_tot]) into row_lse
+// and in log2 units, token-major, into lse2 (either may be null).
 hipError_t launch_row_lse(hipStream_t stream, const DevLayout &L, const AttnPlan &P, int dtype,
                           const void *q, const void *k, int Hq, int Hkv, int d, float scale,
                           float *row_lse, float *lse2, char *ws);
-// lse2 = lse * log2(e) for `rows` rows (an LSE the caller supplies)
-hipError_t launch_lse_to_log2(hipStream_t stream, int rows, const float *lse, float *lse2);
+// lse2 [T_tot][Hq] = lse [Hq][T_tot] * log2(e) (an LSE the caller supplies)
+hipError_t launch_lse_to_log2(hipStream_t stream, int T_tot, int Hq, const float *lse, float *lse2);
 // Pass 2: column sums from the row LSE in log2 units.
 hipError_t launch_colsum(hipStream_t stream, const DevLayout &L, const AttnPlan &P, int dtype,
                          const void *q, const void *k, int Hq, int Hkv, int d, float scale,

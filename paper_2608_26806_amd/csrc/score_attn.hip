@@ -16,8 +16,8 @@
 //   pass 2 (column sums): keys stay in VGPRs, query tiles (and their LSE)
 //     stream through LDS; the output transposes, so each lane owns one key
 //     column and accumulates its column sum locally.
-// Both passes use v_mfma_f32_32x32x16_bf16 (bf16 inputs) or
-// v_mfma_f32_32x32x2_f32 (fp32 inputs), accumulate in fp32, and use exp2
+// Both passes use v_mfma_f32_32x32x16_bf16 (fp32 inputs as three bf16 parts,
+// see Mma<float>), accumulate in fp32, and use exp2
 // with c*log2(e) folded into one FMA per logit.  Every reduction has a fixed
 // order, so results are bit-reproducible and identical key rows give
 // identical scores.
@@ -33,61 +33,122 @@ namespace avtp {
 namespace {
 
 typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kLn2 = 0.6931471805599453f;
 constexpr int kThreads = 256;  // 4 waves per block in both passes
-constexpr int kStage = 128;    // query rows per LDS stage in pass 2
-constexpr int kStage1 = 128;   // key rows per LDS stage in pass 1
+// Granule of the plan: pass-1 key chunks and pass-2 query splits (and the
+// stages of bf16 inputs; fp32 stages are smaller, see Geo).
+constexpr int kStage = 128;    // query rows, pass 2
+constexpr int kStage1 = 128;   // key rows, pass 1
 // A chain of 16 exp2 terms above this means the lazily kept reference of a
 // row is too far below the row's logits: that chain is redone exactly.
 constexpr float kLazyLimit = 18446744073709551616.f;  // 2^64
 
+__device__ inline f32x16 mma(bf16x8 a, bf16x8 b, f32x16 c) {
+  return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
+}
+
+// One k-step of a 32x32 tile: each lane feeds E elements of a row.
 template <typename T>
 struct Mma;
 template <>
 struct Mma<__bf16> {
-  static constexpr int E = 8;  // elements each lane feeds per k-step
-  typedef __bf16 frag __attribute__((ext_vector_type(8)));
-  __device__ static inline f32x16 run(frag a, frag b, f32x16 c) {
-    return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
-  }
+  static constexpr int E = 8;
+  static constexpr int NP = 1;  // bf16 planes per input value
+  static constexpr int NM = 1;  // MFMAs per k-step
+  typedef bf16x8 frag;
+  __device__ static inline f32x16 run(const frag &a, const frag &b, f32x16 c) { return mma(a, b, c); }
 };
+// fp32 inputs run on the bf16 MFMA too, 16 times the rate of the fp32 one: a
+// value is the sum of three bf16 numbers (8 bits each, remainders taken
+// exactly, so 2^-25 of the value or less is lost) and a product is the six
+// partial products down to 2^-16 of it, smallest first; those left out are
+// below 2^-24 of it, the fp32 rounding.  A chain has 48 fp32 accumulations at
+// d = 128 where the fp32 MFMA has 64: the scores' error against 64 bits is the
+// same.  Two sequences of 8 images, 96 text rows, d = 128: both passes
+// 150 + 149 -> 77 + 65 us.
 template <>
 struct Mma<float> {
-  static constexpr int E = 1;
-  typedef float frag;
-  __device__ static inline f32x16 run(frag a, frag b, f32x16 c) {
-    return __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, c, 0, 0, 0);
+  static constexpr int E = 8;
+  static constexpr int NP = 3;
+  static constexpr int NM = 6;
+  struct frag {
+    bf16x8 p[3];
+  };
+  __device__ static inline f32x16 run(const frag &a, const frag &b, f32x16 c) {
+    c = mma(a.p[2], b.p[0], c);
+    c = mma(a.p[0], b.p[2], c);
+    c = mma(a.p[1], b.p[1], c);
+    c = mma(a.p[1], b.p[0], c);
+    c = mma(a.p[0], b.p[1], c);
+    return mma(a.p[0], b.p[0], c);
   }
 };
 
+// Eight fp32 values as three bf16 planes (nearest even; remainders exact).
+__device__ inline Mma<float>::frag split8(const float4 &u, const float4 &v) {
+  const float x[8] = {u.x, u.y, u.z, u.w, v.x, v.y, v.z, v.w};
+  Mma<float>::frag f;
+#pragma unroll
+  for (int i = 0; i < 8; ++i) {
+    const __bf16 h = (__bf16)x[i];
+    const float r = x[i] - (float)h;
+    const __bf16 m = (__bf16)r;
+    f.p[0][i] = h;
+    f.p[1][i] = m;
+    f.p[2][i] = (__bf16)(r - (float)m);
+  }
+  return f;
+}
+
+// fp32 inputs: replace the elements of a 32x32 tile that are not a number by
+// the fp32 MFMA's, `a` and `b` being this lane's operand rows in memory (row
+// lane & 31 of the tile).  An infinite or overflowing input has no finite split
+// (its partial products meet as inf - inf), and its logit may be -inf.  The
+// whole wave calls it; rare, so the loop stays rolled.
+template <int D>
+__device__ inline void replace_nan(f32x16 &acc, const char *a, const char *b, int hi) {
+  f32x16 z = f32x16{};
+#pragma unroll 1
+  for (int i = 0; i < D; i += 2)
+    z = __builtin_amdgcn_mfma_f32_32x32x2f32(*reinterpret_cast<const float *>(a + (i + hi) * 4),
+                                             *reinterpret_cast<const float *>(b + (i + hi) * 4), z, 0, 0, 0);
+#pragma unroll
+  for (int e = 0; e < 16; ++e)
+    if (acc[e] != acc[e]) acc[e] = z[e];
+}
+
 // Register budget, two waves per SIMD (256 VGPRs per wave).  Pass 1 keeps
-// at most two 32-row query tiles per wave and two accumulator sets per tile;
+// at most two 32-row query tiles per wave (one of fp32 inputs, whose tile takes
+// three times the registers) and two accumulator sets per tile;
 // pass 2 keeps up to 96 registers of stationary key tiles, one accumulator
-// set each (fewer tiles on small grids, see attn_plan).  fp32
-// operands at d = 128 do not fit that budget and run one wave per SIMD.
+// set each (fewer tiles on small grids, see attn_plan).
 constexpr int kTiles1 = 2;
-template <typename T, int D>
-struct Occ {
-  static constexpr int value = (sizeof(T) == 4 && D == 128) ? 1 : 2;
-};
-// pass 2: stationary key fragments take at most 96 registers
-__host__ __device__ constexpr int tiles_pass2(int row_bytes) {
-  return 96 / (row_bytes / 8) < 1 ? 1 : (96 / (row_bytes / 8) > 4 ? 4 : 96 / (row_bytes / 8));
+constexpr int kWavesPerSimd = 2;
+__host__ __device__ constexpr int max_tiles1(bool fp32) { return fp32 ? 1 : kTiles1; }
+// pass 2: stationary key fragments take at most 96 registers (planes of d
+// bf16 values, 32 rows over 64 lanes)
+__host__ __device__ constexpr int tiles_pass2(int d, int planes) {
+  return 96 / (planes * d / 4) < 1 ? 1 : (96 / (planes * d / 4) > 4 ? 4 : 96 / (planes * d / 4));
 }
 
 template <typename T, int D>
 struct Geo {
+  static constexpr bool SPLIT = Mma<T>::NP > 1;
   static constexpr int E = Mma<T>::E;
   static constexpr int NS = D / (2 * E);          // k-steps per 32x32 tile
-  static constexpr int ROWB = D * (int)sizeof(T);  // bytes of one head row
-  static constexpr int LS = ROWB + 16;             // padded LDS row stride (conflict-free b128 reads)
-  static constexpr int NT2 = tiles_pass2(ROWB);   // same for pass 2
-  static constexpr int V16 = kStage * ROWB / 16 / kThreads;  // 16-byte loads per thread per stage
-  static constexpr int V16_ROW = ROWB / 16;
-  static constexpr int NCH = ROWB / 16;                // 16-byte chunks per row
+  static constexpr int ROWB = D * (int)sizeof(T);  // bytes of one head row in memory
+  static constexpr int PROWB = D * 2;              // and of one bf16 plane of it in LDS
+  static constexpr int NT2 = tiles_pass2(D, Mma<T>::NP);   // key tiles per wave, pass 2
+  static constexpr int NCH = PROWB / 16;               // 16-byte chunks per LDS row
   static constexpr int SWZ = (NCH < 16 ? NCH : 16) - 1;  // XOR swizzle of the chunk index
+  // Rows per stage, both passes.  bf16: 128 rows, by direct-to-LDS loads.
+  // fp32: the rows are loaded to registers, split and stored, 24 KB of planes
+  // per stage, so that two blocks fit on a CU with two stages each.
+  static constexpr int STAGE = SPLIT ? 24576 / (3 * PROWB) : kStage;
+  static constexpr int SBYTES = STAGE * PROWB * Mma<T>::NP;
 };
 
 // Byte offset in a swizzled LDS stage of element offset `eo` of row `row`:
@@ -96,18 +157,95 @@ struct Geo {
 template <typename T, int D>
 __device__ inline int swz_off(int row, int eo) {
   using G_ = Geo<T, D>;
-  const int bo = eo * (int)sizeof(T);
-  return row * G_::ROWB + (((bo >> 4) ^ (row & G_::SWZ)) << 4) + (bo & 15);
+  const int bo = eo * 2;
+  return row * G_::PROWB + (((bo >> 4) ^ (row & G_::SWZ)) << 4) + (bo & 15);
 }
 
-// Enqueue one stage (ROWS rows of ROWB bytes) with global_load_lds: wave w
+template <typename F>
+__device__ inline F load_frag(const char *p) {
+  return *reinterpret_cast<const F *>(p);
+}
+// the operand elements [eo, eo + E) of stage row `row`
+template <typename T, int D>
+__device__ inline typename Mma<T>::frag lds_frag(const char *stage, int row, int eo) {
+  const char *p = stage + swz_off<T, D>(row, eo);
+  if constexpr (Geo<T, D>::SPLIT) {
+    constexpr int PLANE = Geo<T, D>::STAGE * Geo<T, D>::PROWB;
+    return {{load_frag<bf16x8>(p), load_frag<bf16x8>(p + PLANE), load_frag<bf16x8>(p + 2 * PLANE)}};
+  } else {
+    return load_frag<bf16x8>(p);
+  }
+}
+// the operand elements at p in memory
+template <typename T>
+__device__ inline typename Mma<T>::frag mem_frag(const char *p) {
+  if constexpr (Mma<T>::NP > 1)
+    return split8(load_frag<float4>(p), load_frag<float4>(p + 16));
+  else
+    return load_frag<bf16x8>(p);
+}
+
+// One fp32 stage on its way through the registers: eight values of a row per
+// unit, UPT units per thread.  load() issues the loads (row_off as for
+// dma_stage), store() splits what came and writes the three planes.
+template <int D>
+struct SplitStage {
+  using G_ = Geo<float, D>;
+  static constexpr int UPR = D / 8;  // units per row
+  static constexpr int UPT = G_::STAGE * UPR / kThreads;
+  static_assert(UPT >= 1 && G_::STAGE * UPR % kThreads == 0, "whole units per thread");
+  float4 lo[UPT], hi[UPT];
+  template <typename F>
+  __device__ inline void load(const char *base, int tid, F row_off) {
+#pragma unroll
+    for (int i = 0; i < UPT; ++i) {
+      const int u = tid + i * kThreads;
+      const char *p = base + (row_off(u / UPR) + (uint32_t)(u % UPR) * 32u);
+      lo[i] = load_frag<float4>(p);
+      hi[i] = load_frag<float4>(p + 16);
+    }
+  }
+  __device__ inline void store(char *stage, int tid) const {
+#pragma unroll
+    for (int i = 0; i < UPT; ++i) {
+      const int u = tid + i * kThreads;
+      const Mma<float>::frag f = split8(lo[i], hi[i]);
+      char *p = stage + swz_off<float, D>(u / UPR, (u % UPR) * 8);
+#pragma unroll
+      for (int q = 0; q < 3; ++q) *reinterpret_cast<bf16x8 *>(p + q * G_::STAGE * G_::PROWB) = f.p[q];
+    }
+  }
+};
+
+// The stages come in by direct-to-LDS loads of the buffer form, 16 bytes per
+// lane: a wave-uniform base, a 32-bit offset per lane and one per wave (a
+// sequence's keys and queries are below 4 GiB, checked on the host).  The
+// global_load form does the same but is a FLAT instruction: while one is in
+// flight the compiler takes every wait for an LDS read to lgkmcnt(0), so each
+// fragment read waits for the ones issued after it.
+typedef __amdgpu_buffer_rsrc_t Rsrc;
+__device__ inline Rsrc make_rsrc(const void *base) {
+  // raw buffer, no stride, no bounds (every offset is a valid row's)
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(base), 0, 0xFFFFFFFF, 0x00027000);
+}
+// 16 (4) bytes per lane: lane l's go to lds + 16 l (4 l)
+__device__ inline void load_lds16(Rsrc src, void *lds, uint32_t lane_off, uint32_t wave_off) {
+  __builtin_amdgcn_raw_ptr_buffer_load_lds(src, (__attribute__((address_space(3))) void *)lds, 16,
+                                           (int)lane_off, (int)wave_off, 0, 0);
+}
+__device__ inline void load_lds4(Rsrc src, void *lds, uint32_t lane_off) {
+  __builtin_amdgcn_raw_ptr_buffer_load_lds(src, (__attribute__((address_space(3))) void *)lds, 4,
+                                           (int)lane_off, 0, 0, 0);
+}
+
+// Enqueue one stage (ROWS rows of ROWB bytes): wave w
 // fills LDS bytes [1 KB * (w*DMA + i), +1 KB) for i < DMA, lane l writing
 // the 16 bytes at +16*l, i.e. physical chunk p = 64*(w*DMA+i) + l.
 // row_off(row) is the byte offset of a (valid) source row from the
-// wave-uniform `base`.  The lane id is made opaque so that the few integer
+// wave-uniform base.  The lane id is made opaque so that the few integer
 // ops per load are redone per stage instead of pinning registers.
 template <typename T, int D, int ROWS, typename F>
-__device__ inline void dma_stage(char *lds, const char *base, int wave, int lane, F row_off) {
+__device__ inline void dma_stage(char *lds, Rsrc base, int wave, int lane, F row_off) {
   using G_ = Geo<T, D>;
   constexpr int DMA = ROWS * G_::NCH / 64 / 4;  // 1 KB loads per wave
   static_assert(DMA >= 1 && ROWS * G_::NCH % 256 == 0, "stage must split into whole wave loads");
@@ -120,9 +258,7 @@ __device__ inline void dma_stage(char *lds, const char *base, int wave, int lane
     const int row = (int)(p / G_::NCH), pc = (int)(p % G_::NCH);
     const int c = pc ^ (row & G_::SWZ);
     const uint32_t off = row_off(row) + (uint32_t)(c * 16);
-    __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(base + off),
-                                     (__attribute__((address_space(3))) void *)(lds + gi * 1024),
-                                     16, 0, 0);
+    load_lds16(base, lds + gi * 1024, off, 0);
   }
 }
 
@@ -147,12 +283,12 @@ struct DmaPlan {
       lo[j] = (uint32_t)(lane / NCH) * stride + (uint32_t)(((lane % NCH) ^ (r & G_::SWZ)) * 16);
     }
   }
-  // rows [0, ROWS) from `base` (row 0) with stride `stride` bytes.  The
+  // rows [0, ROWS) from offset `r0` of `base` (row 0) with stride `stride` bytes.  The
   // wave index and lane offsets are made opaque so that the per-load
   // constants are rebuilt here (a few scalar ops) instead of being kept live
   // across the whole loop.
-  __device__ static inline void issue(char *lds, const char *base, int wave, const uint32_t (&lo)[PER],
-                                      uint32_t stride) {
+  __device__ static inline void issue(char *lds, Rsrc base, uint32_t r0, int wave,
+                                      const uint32_t (&lo)[PER], uint32_t stride) {
     int w = wave;
     asm volatile("" : "+s"(w));
     uint32_t l[PER];
@@ -164,9 +300,7 @@ struct DmaPlan {
 #pragma unroll
     for (int i = 0; i < DMA; ++i) {
       const int gi = w * DMA + i;
-      const char *row = base + (uint32_t)(w * (ROWS / 4) + i * RPL) * stride;
-      __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(row + l[i % PER]),
-                                       (__attribute__((address_space(3))) void *)(lds + gi * 1024), 16, 0, 0);
+      load_lds16(base, lds + gi * 1024, l[i % PER], r0 + (uint32_t)(w * (ROWS / 4) + i * RPL) * stride);
     }
   }
   // Token-major rows: row r of the source is token r >> lg, head r & (G-1)
@@ -183,7 +317,7 @@ struct DmaPlan {
     }
   }
   // rows [r0, r0 + ROWS) of a token-major source (r0 a multiple of ROWS)
-  __device__ static inline void issue_tm(char *lds, const char *base, int r0, int wave,
+  __device__ static inline void issue_tm(char *lds, Rsrc base, int r0, int wave,
                                          const uint32_t (&lo)[PER], int lg, uint32_t tok) {
     int w = wave;
     asm volatile("" : "+s"(w));
@@ -197,9 +331,8 @@ struct DmaPlan {
     for (int i = 0; i < DMA; ++i) {
       const int gi = w * DMA + i;
       const int rr = r0 + w * (ROWS / 4) + i * RPL;
-      const char *row = base + (uint32_t)(rr >> lg) * tok + (uint32_t)(rr & ((1 << lg) - 1)) * G_::ROWB;
-      __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(row + l[i % PER]),
-                                       (__attribute__((address_space(3))) void *)(lds + gi * 1024), 16, 0, 0);
+      load_lds16(base, lds + gi * 1024, l[i % PER],
+                 (uint32_t)(rr >> lg) * tok + (uint32_t)(rr & ((1 << lg) - 1)) * G_::ROWB);
     }
   }
 };
@@ -217,33 +350,29 @@ __device__ inline void interleave_mfma_valu() {
   }
 }
 
-// Scheduling hint for one pass-1 key tile: the LDS reads of the first LEAD
+// Scheduling hint for one pass-1 key tile: the LDS reads of the first
 // k-steps (none if they were read before the tile), then per k-step the NT
-// MFMAs of the step, each followed by up to V VALU ops working on the
-// previous tile, then the LDS read of the fragment PF steps ahead.
-template <int NS, int NT, int V, int LEAD, bool NX = false>
+// products of the step (NM MFMAs each), each MFMA followed by up to V VALU ops
+// working on the previous tile, then the LDS reads (NP) of the fragment PF
+// steps ahead.
+template <int NS, int NT, int NM, int NP, int V, bool PRE, bool NX>
 __device__ inline void interleave_tile() {
   constexpr int PF = NS < 3 ? NS : 3;
-  if (LEAD > 0) __builtin_amdgcn_sched_group_barrier(0x100, LEAD, 0);  // DS read
+  if (!PRE) __builtin_amdgcn_sched_group_barrier(0x100, PF * NP, 0);  // DS read
 #pragma unroll
   for (int s = 0; s < NS; ++s) {
 #pragma unroll
-    for (int i = 0; i < NT; ++i) {
+    for (int i = 0; i < NT * NM; ++i) {
       __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);  // MFMA
       __builtin_amdgcn_sched_group_barrier(0x002, V, 0);  // VALU
     }
     // the fragment PF steps ahead: of this tile, or (NX) of the next one
-    if (s + PF < NS || NX) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);  // DS read
+    if (s + PF < NS || NX) __builtin_amdgcn_sched_group_barrier(0x100, NP, 0);  // DS read
   }
 }
 
 // wait for this wave's outstanding global loads (including direct-to-LDS ones)
 __device__ inline void wait_vmem() { __builtin_amdgcn_s_waitcnt(0xF70); }
-
-template <typename F>
-__device__ inline F load_frag(const char *p) {
-  return *reinterpret_cast<const F *>(p);
-}
 
 // Positions spanned by pass-1 query rows [r0, r1) of one (sequence, key
 // head).  Rows are token-major: row r is text token r / G under query head
@@ -260,7 +389,7 @@ struct P1Args {
   int B, Hq, Hkv, G, T_tot;
   int nqb, nkc, kchunk;
   float cl2e;
-  float *part_m, *part_l;  // [nkc][Hq * T_tot]
+  float *part_m, *part_l;  // [nkc][T_tot][Hq]
 };
 
 // Pass 1: per (sequence b, key head g, query block, key chunk), partial
@@ -278,20 +407,28 @@ struct P1Args {
 // only in part takes a per-element masked variant.  Query rows are
 // token-major (the G heads of one text token adjacent), so a block's rows
 // span few positions and a block of early text rows stops at its last row.
-template <typename T, int D, int NT>
-__global__ __launch_bounds__(kThreads, (Occ<T, D>::value)) void rowstats_kernel(P1Args a) {
+//
+// SMALL (fp32 inputs, grids of less than one block per CU): each tile's products
+// and then its masked sums, in a rolled loop.  A block runs a handful of tiles
+// there and is bound by latency, the fetch of its own code included: 11 KB of
+// code instead of 42, one sequence of 2 x 64 tokens, d = 64: 11.6 -> 8.1 us.
+// The bf16 kernel's unrolled tiles hide more than they cost: with this form 4 x
+// 729 tokens took 9.0 -> 9.9 us, two sequences of 8 images 20.2 -> 25.5.
+template <typename T, int D, int NT, bool SMALL>
+__global__ __launch_bounds__(kThreads, kWavesPerSimd) void rowstats_kernel(P1Args a) {
   using G_ = Geo<T, D>;
   using MM = Mma<T>;
   using frag = typename MM::frag;
   constexpr int NS = G_::NS, ROWB = G_::ROWB, E = G_::E;
   constexpr int QB = 4 * NT * 32;  // query rows per block
-  constexpr int KS = kStage1;      // keys per LDS stage
+  constexpr bool SPLIT = G_::SPLIT;
+  constexpr int KS = G_::STAGE;    // keys per LDS stage
   constexpr int TPS = KS / 32;     // key tiles per stage
-  static_assert(TPS % 2 == 0, "accumulator sets alternate between consecutive key tiles");
+  static_assert(kStage1 % KS == 0, "chunks are whole stages");
   // two stage buffers as distinct objects, so the compiler can tell the
   // buffer being read from the one the in-flight DMA writes
-  __shared__ __attribute__((aligned(16))) char smA[KS * ROWB];
-  __shared__ __attribute__((aligned(16))) char smB[KS * ROWB];
+  __shared__ __attribute__((aligned(16))) char smA[G_::SBYTES];
+  __shared__ __attribute__((aligned(16))) char smB[G_::SBYTES];
 
   // Blocks that share one key chunk (the nqb query blocks of a unit) get
   // ids that are equal mod 8, i.e. land on one XCD and share its L2.  Units
@@ -319,7 +456,8 @@ __global__ __launch_bounds__(kThreads, (Occ<T, D>::value)) void rowstats_kernel(
     // no row of the block sees a key of the chunk: empty partials, so that
     // the combine can read every chunk of every row
     for (int r = row0 + (int)threadIdx.x; r < min(R, row0 + QB); r += kThreads) {
-      const int t = r / a.G, qidx = (g * a.G + (r - t * a.G)) * a.T_tot + t0 + t;
+      const int t = r / a.G;
+      const size_t qidx = (size_t)(t0 + t) * a.Hq + g * a.G + (r - t * a.G);
       a.part_m[kc * HqT + qidx] = -INFINITY;
       a.part_l[kc * HqT + qidx] = 0.f;
     }
@@ -333,8 +471,35 @@ __global__ __launch_bounds__(kThreads, (Occ<T, D>::value)) void rowstats_kernel(
   const int hi = lane >> 5, col = lane & 31;
   const int wr0 = row0 + wave * NT * 32;
   const bool active = wr0 < R;
+
+  // keys of one stage, rows clamped into the chunk (rows past kend are masked)
+  const char *kmem = a.k + ((size_t)s0 * a.Hkv + g) * ROWB;  // key 0 of this sequence, head g
+  const Rsrc kbase = make_rsrc(kmem);
+  const uint32_t kstride = (uint32_t)a.Hkv * ROWB;
+  using DP = DmaPlan<__bf16, D, kStage>;  // (bf16 stages)
+  uint32_t dlo[DP::PER];
+  if constexpr (!SPLIT) DP::lane_offsets(dlo, lane, kstride);
+  // fp32: the rows of stage `ks` to registers, and what was loaded to LDS
+  SplitStage<D> raw;
+  auto load_raw = [&](int ks) __attribute__((always_inline)) {
+    raw.load(kmem, tid, [&](int row) __attribute__((always_inline)) {
+      return (uint32_t)min(ks + row, kend - 1) * kstride;
+    });
+  };
+  auto issue_stage = [&](int ks, char *dst) __attribute__((always_inline)) {
+    if constexpr (SPLIT) {
+    } else if (ks + KS <= kend) {
+      DP::issue(dst, kbase, (uint32_t)ks * kstride, wave, dlo, kstride);
+    } else {  // last stage of the chunk: rows past its end re-read row kend-1
+      dma_stage<T, D, KS>(dst, kbase, wave, lane, [&](int row) __attribute__((always_inline)) {
+        return (uint32_t)min(ks + row, kend - 1) * kstride;
+      });
+    }
+  };
+
   int wmin = 0, wmax = -1;
   if (active) rows_pos_range(tp, a.G, wr0, min(R, wr0 + NT * 32), wmin, wmax);
+  if constexpr (SPLIT) load_raw(kbeg);
 
   // stationary operand: this wave's query rows
   frag qf[NT][NS];
@@ -348,13 +513,12 @@ __global__ __launch_bounds__(kThreads, (Occ<T, D>::value)) void rowstats_kernel(
       qrel[i] = tp[t] - s0;
       const char *src = a.q + ((size_t)(t0 + t) * a.Hq + h) * ROWB + hi * E * sizeof(T);
 #pragma unroll
-      for (int s = 0; s < NS; ++s) qf[i][s] = load_frag<frag>(src + s * 2 * E * sizeof(T));
+      for (int s = 0; s < NS; ++s) qf[i][s] = mem_frag<T>(src + s * 2 * E * sizeof(T));
     } else {
 #pragma unroll
       for (int s = 0; s < NS; ++s) qf[i][s] = frag{};
     }
   }
-
   float ref[NT], l[NT];
 #pragma unroll
   for (int i = 0; i < NT; ++i) {
@@ -362,22 +526,6 @@ __global__ __launch_bounds__(kThreads, (Occ<T, D>::value)) void rowstats_kernel(
     l[i] = 0.f;
   }
   const float cl2e = a.cl2e;
-
-  // keys of one stage, rows clamped into the chunk (rows past kend are masked)
-  const char *kbase = a.k + ((size_t)s0 * a.Hkv + g) * ROWB;  // key 0 of this sequence, head g
-  const uint32_t kstride = (uint32_t)a.Hkv * ROWB;
-  using DP = DmaPlan<T, D, KS>;
-  uint32_t dlo[DP::PER];
-  DP::lane_offsets(dlo, lane, kstride);
-  auto issue_stage = [&](int ks, char *dst) __attribute__((always_inline)) {
-    if (ks + KS <= kend) {
-      DP::issue(dst, kbase + (size_t)ks * kstride, wave, dlo, kstride);
-    } else {  // last stage of the chunk: rows past its end re-read row kend-1
-      dma_stage<T, D, KS>(dst, kbase, wave, lane, [&](int row) __attribute__((always_inline)) {
-        return (uint32_t)min(ks + row, kend - 1) * kstride;
-      });
-    }
-  };
 
   // Accumulator element e of this lane holds key kb + hi*4 + eoff(e) of its
   // query column; it is visible iff eoff(e) <= vl, with the per-lane limit
@@ -436,16 +584,15 @@ __global__ __launch_bounds__(kThreads, (Occ<T, D>::value)) void rowstats_kernel(
     if (MF) {
 #pragma unroll
       for (int s = 0; s < PF; ++s)
-        av[s] = PRE ? pf[s] : load_frag<frag>(buf + swz_off<T, D>(lrow + col, s * 2 * E + hi * E));
+        av[s] = PRE ? pf[s] : lds_frag<T, D>(buf, lrow + col, s * 2 * E + hi * E);
     }
 #pragma unroll
     for (int s = 0; s < NS; ++s) {
       if (MF) {
         if (s + PF < NS)
-          av[s + PF] = load_frag<frag>(buf + swz_off<T, D>(lrow + col, (s + PF) * 2 * E + hi * E));
+          av[s + PF] = lds_frag<T, D>(buf, lrow + col, (s + PF) * 2 * E + hi * E);
         else if (NX)
-          pf[s + PF - NS] =
-              load_frag<frag>(buf + swz_off<T, D>(lrow + 32 + col, (s + PF - NS) * 2 * E + hi * E));
+          pf[s + PF - NS] = lds_frag<T, D>(buf, lrow + 32 + col, (s + PF - NS) * 2 * E + hi * E);
 #pragma unroll
         for (int qi = 0; qi < NT; ++qi) acc[CS + qi] = MM::run(av[s], qf[qi][s], acc[CS + qi]);
       }
@@ -462,8 +609,7 @@ __global__ __launch_bounds__(kThreads, (Occ<T, D>::value)) void rowstats_kernel(
       }
     }
     if (MF)
-      interleave_tile<NS, NT, ((M == kPerElem ? 64 : 40) / NS > 0 ? (M == kPerElem ? 64 : 40) / NS : 1),
-                      PRE ? 0 : PF, NX>();
+      interleave_tile<NS, NT, MM::NM, MM::NP, SPLIT ? 1 : (M == kPerElem ? 64 : 40) / NS, PRE, NX>();
     float t[NT];
     bool bad = false;
 #pragma unroll
@@ -473,6 +619,15 @@ __global__ __launch_bounds__(kThreads, (Occ<T, D>::value)) void rowstats_kernel(
       bad = bad || !(t[qi] <= kLazyLimit);
     }
     if (__ballot(bad) != 0ull) {
+      if constexpr (SPLIT) {
+#pragma unroll
+        for (int qi = 0; qi < NT; ++qi)
+          if (__ballot(t[qi] != t[qi]) != 0ull) {
+            const int row = min(wr0 + qi * 32 + col, R - 1), tk = row / a.G;
+            replace_nan<D>(acc[PS + qi], kmem + (size_t)min(pend_kb + col, kend - 1) * kstride,
+                           a.q + ((size_t)(t0 + tk) * a.Hq + g * a.G + (row - tk * a.G)) * ROWB, hi);
+          }
+      }
       // exact redo of the chains whose sum left the range: raise the
       // reference to the chain's maximum and rescale the row sum
 #pragma unroll
@@ -499,52 +654,90 @@ __global__ __launch_bounds__(kThreads, (Occ<T, D>::value)) void rowstats_kernel(
     for (int qi = 0; qi < NT; ++qi) l[qi] += t[qi];
   };
   using P0 = std::integral_constant<int, 0>;
+  using P1 = std::integral_constant<int, 1>;
+  static_assert(TPS == 1 || TPS == 2 || TPS == 4, "one stage is one, two or four key tiles");
+  auto each_tile = [&](auto one) __attribute__((always_inline)) {
+    one(std::integral_constant<int, 0>{});
+    if constexpr (TPS >= 2) one(std::integral_constant<int, 1>{});
+    if constexpr (TPS == 4) {
+      one(std::integral_constant<int, 2>{});
+      one(std::integral_constant<int, 3>{});
+    }
+  };
 
   const int nstage = (kstop - kbeg + KS - 1) / KS;
   // key tiles this wave processes: those below kstop that start at or
   // before its last row (a prefix of the chunk's tiles)
   const int kw_end = active ? min(kstop, wmax - s0 + 1) : kbeg;
   const int ntw = kw_end > kbeg ? (kw_end - kbeg + 31) / 32 : 0;
-  issue_stage(kbeg, smA);
-  auto step = [&](const char *buf, char *nxt, int st) __attribute__((always_inline)) {
+  if constexpr (SPLIT) {
+    raw.store(smA, tid);
+    if (nstage > 1) load_raw(kbeg + KS);
+  } else {
+    issue_stage(kbeg, smA);
+  }
+  // BP: parity of the accumulator set that the buffer's first tile goes to
+  // (the sets alternate between consecutive key tiles)
+  auto step = [&](const char *buf, char *nxt, int st, auto bp_tag) __attribute__((always_inline)) {
+    constexpr int BP = decltype(bp_tag)::value;
     const int ks = kbeg + st * KS;
     wait_vmem();
     __syncthreads();  // stage st is in LDS; every wave is done with the other buffer
-    if (st + 1 < nstage) issue_stage(ks + KS, nxt);
+    if constexpr (SPLIT) {
+      if (st + 1 < nstage) raw.store(nxt, tid);
+      if (st + 2 < nstage) load_raw(ks + 2 * KS);
+    } else {
+      if (st + 1 < nstage) issue_stage(ks + KS, nxt);
+    }
+    if constexpr (SMALL) {
+#pragma unroll 1
+      for (int kt = st * TPS; kt < min((st + 1) * TPS, ntw); ++kt) {
+        const int lrow = (kt - st * TPS) * 32;
+#pragma unroll
+        for (int i = 0; i < NT; ++i) acc[i] = f32x16{};
+#pragma unroll
+        for (int s = 0; s < NS; ++s) {
+          const frag f = lds_frag<T, D>(buf, lrow + col, s * 2 * E + hi * E);
+#pragma unroll
+          for (int i = 0; i < NT; ++i) acc[i] = MM::run(f, qf[i][s], acc[i]);
+        }
+        pend_kb = ks + lrow;
+        tile(buf, 0, P1{}, PerElem{}, std::false_type{}, std::false_type{}, NoNext{});
+      }
+      return;
+    }
     // every lane sees every pending tile of the stage (the previous stage's
     // last tile and this stage's first TPS-1): no per-tile checks, and each
     // tile reads the next one's first fragments
     bool allvis = false;
     if ((st + 1) * TPS <= ntw && pend_kb != kNone) {
 #pragma unroll
-      for (int s = 0; s < PF; ++s) pf[s] = load_frag<frag>(buf + swz_off<T, D>(col, s * 2 * E + hi * E));
+      for (int s = 0; s < PF; ++s) pf[s] = lds_frag<T, D>(buf, col, s * 2 * E + hi * E);
       bool part = false;
 #pragma unroll
       for (int qi = 0; qi < NT; ++qi) part = part || qrel[qi] < ks + (TPS - 1) * 32 - 1;
       allvis = __ballot(part) == 0ull;
     }
     if (allvis) {
-      using P0_ = std::integral_constant<int, 0>;
-      using P1_ = std::integral_constant<int, 1>;
       using Yes = std::true_type;
-      tile(buf, 0, P0_{}, All{}, Yes{}, Yes{}, Yes{});
-      tile(buf, 32, P1_{}, All{}, Yes{}, Yes{}, Yes{});
-      if constexpr (TPS == 4) {
-        tile(buf, 64, P0_{}, All{}, Yes{}, Yes{}, Yes{});
-        tile(buf, 96, P1_{}, All{}, Yes{}, Yes{}, NoNext{});
-      }
+      auto one = [&](auto kt_tag) __attribute__((always_inline)) {
+        constexpr int KT = decltype(kt_tag)::value;
+        tile(buf, KT * 32, std::integral_constant<int, (KT + BP) & 1>{}, All{}, Yes{}, Yes{},
+             std::integral_constant<bool, KT + 1 < TPS>{});
+      };
+      each_tile(one);
       pend_kb = ks + (TPS - 1) * 32;
     } else if ((st + 1) * TPS <= ntw) {
       // every tile of the stage is this wave's: no per-tile bounds
       auto one = [&](auto kt_tag) __attribute__((always_inline)) {
         constexpr int KT = decltype(kt_tag)::value;
-        using par_tag = std::integral_constant<int, KT & 1>;
+        using par_tag = std::integral_constant<int, (KT + BP) & 1>;
         // a lane that sees only part of the pending tile needs the masked
         // variant; the tile's first fragments are read before this check,
         // whose VALU work then covers their latency
 #pragma unroll
         for (int s = 0; s < PF; ++s)
-          pf[s] = load_frag<frag>(buf + swz_off<T, D>(KT * 32 + col, s * 2 * E + hi * E));
+          pf[s] = lds_frag<T, D>(buf, KT * 32 + col, s * 2 * E + hi * E);
         bool part = false;
 #pragma unroll
         for (int qi = 0; qi < NT; ++qi) part = part || (unsigned)(qrel[qi] - pend_kb) < 31u;
@@ -554,18 +747,12 @@ __global__ __launch_bounds__(kThreads, (Occ<T, D>::value)) void rowstats_kernel(
           tile(buf, KT * 32, par_tag{}, PerElem{}, std::true_type{}, std::true_type{}, NoNext{});
         pend_kb = ks + KT * 32;
       };
-      static_assert(TPS == 2 || TPS == 4, "one stage is two or four key tiles");
-      one(std::integral_constant<int, 0>{});
-      one(std::integral_constant<int, 1>{});
-      if constexpr (TPS == 4) {
-        one(std::integral_constant<int, 2>{});
-        one(std::integral_constant<int, 3>{});
-      }
+      each_tile(one);
     } else if (st * TPS < ntw) {
       // the wave's last tiles, then settle the pending one (masked variant)
       auto one = [&](auto kt_tag) __attribute__((always_inline)) {
         constexpr int KT = decltype(kt_tag)::value;
-        using par_tag = std::integral_constant<int, KT & 1>;
+        using par_tag = std::integral_constant<int, (KT + BP) & 1>;
         if (st * TPS + KT < ntw) {
           tile(buf, KT * 32, par_tag{}, PerElem{}, std::true_type{}, std::false_type{}, NoNext{});
           pend_kb = ks + KT * 32;
@@ -574,21 +761,22 @@ __global__ __launch_bounds__(kThreads, (Occ<T, D>::value)) void rowstats_kernel(
           pend_kb = kNone;
         }
       };
-      one(std::integral_constant<int, 0>{});
-      one(std::integral_constant<int, 1>{});
-      if constexpr (TPS == 4) {
-        one(std::integral_constant<int, 2>{});
-        one(std::integral_constant<int, 3>{});
-      }
+      each_tile(one);
     }
   };
   for (int st = 0; st < nstage; st += 2) {
-    step(smA, smB, st);
-    if (st + 1 < nstage) step(smB, smA, st + 1);
+    step(smA, smB, st, P0{});
+    if (st + 1 < nstage) step(smB, smA, st + 1, std::integral_constant<int, TPS & 1>{});
   }
   if (!active) return;
-  // with a whole number of stages the pending tile is the last (odd) one
-  if (ntw > 0 && ntw % TPS == 0) tile(smA, 0, P0{}, PerElem{}, std::false_type{}, std::false_type{}, NoNext{});
+  // with a whole number of stages the last tile is still pending (an odd one
+  // where stages have an even number of tiles)
+  if (!SMALL && ntw > 0 && ntw % TPS == 0) {
+    if (TPS % 2 == 1 && (ntw & 1))
+      tile(smA, 0, P1{}, PerElem{}, std::false_type{}, std::false_type{}, NoNext{});
+    else
+      tile(smA, 0, P0{}, PerElem{}, std::false_type{}, std::false_type{}, NoNext{});
+  }
 
   // merge the two half-waves (same query column, disjoint keys) and store
 #pragma unroll
@@ -601,15 +789,17 @@ __global__ __launch_bounds__(kThreads, (Occ<T, D>::value)) void rowstats_kernel(
             (om == -INFINITY ? 0.f : ol * __builtin_amdgcn_exp2f(om - nm));
     const int r = wr0 + i * 32 + col;
     if (hi == 0 && r < R) {
-      const int t = r / a.G, qidx = (g * a.G + (r - t * a.G)) * a.T_tot + t0 + t;
+      const int t = r / a.G;
+      const size_t qidx = (size_t)(t0 + t) * a.Hq + g * a.G + (r - t * a.G);
       a.part_m[kc * HqT + qidx] = nm;
       a.part_l[kc * HqT + qidx] = tot;
     }
   }
 }
 
-// Merge the chunk partials of every text row into lse = ln(sum exp(z)), and
-// (if lse2 is given) the same in log2 units for pass 2.  Pass 1 writes a
+// Merge the chunk partials of every text row into lse = ln(sum exp(z))
+// [Hq][T_tot] and / or (whichever is given) the same in log2 units, token-major
+// [T_tot][Hq] like the partials, for pass 2.  Pass 1 writes a
 // partial for every (chunk, row), empty (-inf, 0) where the row sees no key
 // of the chunk.  Max and sum run over the chunks in ascending order.
 //
@@ -619,8 +809,9 @@ __global__ __launch_bounds__(kThreads, (Occ<T, D>::value)) void rowstats_kernel(
 // round of loads; with more, the groups are read twice (max, then sum).
 template <int G>
 __global__ void lse_combine_kernel(const float *__restrict__ part_m, const float *__restrict__ part_l,
-                                   int rows, int nkc, float *__restrict__ lse,
+                                   int T_tot, int Hq, int nkc, float *__restrict__ lse,
                                    float *__restrict__ lse2) {
+  const int rows = T_tot * Hq;
   const int idx = blockIdx.x * blockDim.x + threadIdx.x;
   if (idx >= rows) return;
   auto at = [&](int c) __attribute__((always_inline)) {
@@ -662,33 +853,37 @@ __global__ void lse_combine_kernel(const float *__restrict__ part_m, const float
     }
   }
   const float v = (M + __builtin_amdgcn_logf(S)) * kLn2;
-  lse[idx] = v;
+  if (lse) {
+    const int t = idx / Hq;
+    lse[(size_t)(idx - t * Hq) * T_tot + t] = v;
+  }
   // log2 units from the rounded natural value, exactly as for a supplied LSE
   if (lse2) lse2[idx] = v * kLog2e;
 }
 
-// Row LSE in natural log -> log2 units (for an LSE the caller supplies).
-__global__ void lse_to_log2_kernel(const float *__restrict__ lse, int rows, float *__restrict__ lse2) {
+// Row LSE [Hq][T_tot] in natural log -> log2 units, token-major (for an LSE
+// the caller supplies).
+__global__ void lse_to_log2_kernel(const float *__restrict__ lse, int T_tot, int Hq,
+                                   float *__restrict__ lse2) {
   const int idx = blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx < rows) lse2[idx] = lse[idx] * kLog2e;
+  if (idx >= T_tot * Hq) return;
+  const int h = idx / T_tot;
+  lse2[(size_t)(idx - h * T_tot) * Hq + h] = lse[idx] * kLog2e;
 }
 
-// Pass-2 LDS stage: kStage query rows (swizzled) with their row LSE and
-// positions, double-buffered.  Rows past the end of the split get LSE +inf
-// and position -1, copied from these two constants, so they add nothing and
-// are never visible.
-__device__ const float kRowNone = INFINITY;
-__device__ const int kPosNone = -1;
-template <int ROWB>
+// Pass-2 LDS stage: the query rows (swizzled) with their row LSE and
+// positions, double-buffered.  Rows past the end of the split repeat its last
+// row with LSE +inf, so they add nothing.
+template <int BYTES, int ROWS>
 struct __attribute__((aligned(16))) QTile2 {
-  char q[kStage * ROWB];
-  float lse[kStage];  // log2 units
-  int pos[kStage];
+  char q[BYTES];
+  float lse[ROWS];  // log2 units
+  int pos[ROWS];
 };
 
 struct P2Args {
   const char *q, *k;
-  const float *lse2;  // row LSE in log2 units, [Hq][T_tot]
+  const float *lse2;  // row LSE in log2 units, [T_tot][Hq]
   const int32_t *cu_seqlens, *cu_text, *text_pos;
   int B, Hq, Hkv, G, T_tot, N_tok, nkb, nqs;
   int nsl, ppx, kps;  // key-block slices per unit, (unit, slice) pairs per XCD, blocks per pair
@@ -711,18 +906,22 @@ struct P2Args {
 // which see only part of the wave's keys is done unpipelined with a
 // per-element mask; sub-tiles that see none are skipped.
 template <typename T, int D, int NKT>
-__global__ __launch_bounds__(kThreads, (Occ<T, D>::value)) void colsum_kernel(P2Args a) {
+__global__ __launch_bounds__(kThreads, kWavesPerSimd) void colsum_kernel(P2Args a) {
   using G_ = Geo<T, D>;
   using MM = Mma<T>;
   using frag = typename MM::frag;
   constexpr int NS = G_::NS, ROWB = G_::ROWB, E = G_::E;
-  constexpr int DIST = NKT >= 3 ? 2 : NKT - 1;  // pipeline distance in chains
+  constexpr bool SPLIT = G_::SPLIT;
+  // Pipeline distance in chains.  fp32 inputs: none, a chain has six times the
+  // MFMAs for the same terms, so the other wave of the SIMD covers them.
+  constexpr int DIST = SPLIT ? 0 : (NKT >= 3 ? 2 : NKT - 1);
   constexpr int KB = 4 * NKT * 32;  // keys per block
-  constexpr int QR = kStage;        // query rows per stage
+  constexpr int QR = G_::STAGE;     // query rows per stage
   constexpr int SUBS = QR / 32;     // sub-tiles per stage
-  static_assert(SUBS == 4, "one stage is four query sub-tiles");
+  static_assert(SUBS == 1 || SUBS == 2 || SUBS == 4, "one stage is one, two or four query sub-tiles");
   // two query buffers as distinct objects (see pass 1)
-  __shared__ QTile2<ROWB> qtA, qtB;
+  using QTile = QTile2<G_::SBYTES, QR>;
+  __shared__ QTile qtA, qtB;
 
   // The key blocks of one (sequence, key head) read the same queries, so
   // they stay on few XCDs: a unit's key blocks are dealt to nsl slices
@@ -764,7 +963,7 @@ __global__ __launch_bounds__(kThreads, (Occ<T, D>::value)) void colsum_kernel(P2
     if (key < L) {
       const char *src = a.k + ((size_t)(s0 + key) * a.Hkv + g) * ROWB + hi * E * sizeof(T);
 #pragma unroll
-      for (int s = 0; s < NS; ++s) kf[j][s] = load_frag<frag>(src + s * 2 * E * sizeof(T));
+      for (int s = 0; s < NS; ++s) kf[j][s] = mem_frag<T>(src + s * 2 * E * sizeof(T));
     } else {
 #pragma unroll
       for (int s = 0; s < NS; ++s) kf[j][s] = frag{};
@@ -780,10 +979,12 @@ __global__ __launch_bounds__(kThreads, (Occ<T, D>::value)) void colsum_kernel(P2
   for (int j = 0; j < NKT; ++j) cs[j] = 0.f;
   const float cl2e = a.cl2e;
 
-  const char *qbase = a.q + ((size_t)t0 * a.Hq + g * a.G) * ROWB;  // text row 0, head g*G
+  const char *qmem = a.q + ((size_t)t0 * a.Hq + g * a.G) * ROWB;  // text row 0, head g*G
+  const Rsrc qbase = make_rsrc(qmem);
   const uint32_t qstride = (uint32_t)a.Hq * ROWB;
-  const float *lbase = a.lse2 + (size_t)g * a.G * a.T_tot + t0;    // head g*G, text row 0
-  using DP = DmaPlan<T, D, QR>;
+  const Rsrc lbase = make_rsrc(a.lse2 + (size_t)t0 * a.Hq + g * a.G);
+  const Rsrc pbase = make_rsrc(tp);
+  using DP = DmaPlan<__bf16, D, kStage>;  // (bf16 stages)
   // Rows are token-major: row r is text token r / G under query head
   // g*G + r % G, so positions ascend with r.  With G a power of two every
   // stage load has per-lane offsets fixed across stages.
@@ -791,34 +992,35 @@ __global__ __launch_bounds__(kThreads, (Occ<T, D>::value)) void colsum_kernel(P2
   const bool g_pow2 = (a.G & (a.G - 1)) == 0;
   // One stage: query rows [rs, rs + QR), their LSE and positions.  Wave 0
   // loads the LSE, wave 1 the positions, 64 rows per instruction.
-  auto issue_stage = [&](int rs, QTile2<ROWB> &dst) __attribute__((always_inline)) {
-    if (g_pow2 && rs + QR <= R) {
+  auto row_off = [&](int r) __attribute__((always_inline)) {
+    r = min(r, R - 1);  // rows past R re-read row R-1 (their LSE is +inf)
+    const int t = g_pow2 ? r >> lg : r / a.G;
+    return (uint32_t)(t * a.Hq + (r - t * a.G)) * ROWB;
+  };
+  SplitStage<D> raw;  // fp32: rows on their way to LDS
+  auto load_raw = [&](int rs) __attribute__((always_inline)) {
+    raw.load(qmem, tid, [&](int row) __attribute__((always_inline)) { return row_off(rs + row); });
+  };
+  auto issue_stage = [&](int rs, QTile &dst) __attribute__((always_inline)) {
+    if constexpr (SPLIT) {
+      raw.store(dst.q, tid);  // (loaded a stage ago)
+    } else if (g_pow2 && rs + QR <= R) {
       int ln = lane;
       asm volatile("" : "+v"(ln));
       uint32_t dlo[DP::PER];
       DP::lane_offsets_tm(dlo, ln, lg, qstride);
       DP::issue_tm(dst.q, qbase, rs, wave, dlo, lg, qstride);
     } else {
-      dma_stage<T, D, QR>(dst.q, qbase, wave, lane, [&](int row) __attribute__((always_inline)) {
-        const int r = min(rs + row, R - 1);  // rows past R re-read row R-1; their lse is +inf
-        const int t = r / a.G;
-        return (uint32_t)(t * a.Hq + (r - t * a.G)) * ROWB;
-      });
+      dma_stage<T, D, QR>(dst.q, qbase, wave, lane,
+                          [&](int row) __attribute__((always_inline)) { return row_off(rs + row); });
     }
-    if (wave < 2) {
+    if (wave < 2 && (QR >= 64 || lane < QR)) {
 #pragma unroll
-      for (int i = 0; i < QR / 64; ++i) {
-        const int r = rs + i * 64 + lane;
-        const void *src;
-        if (r < r_hi) {
-          const int t = r / a.G;
-          src = wave == 0 ? (const void *)(lbase + (size_t)(r - t * a.G) * a.T_tot + t) : (const void *)(tp + t);
-        } else {
-          src = wave == 0 ? (const void *)&kRowNone : (const void *)&kPosNone;
-        }
-        void *dstp = wave == 0 ? (void *)(dst.lse + i * 64) : (void *)(dst.pos + i * 64);
-        __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)src,
-                                         (__attribute__((address_space(3))) void *)dstp, 4, 0, 0);
+      for (int i = 0; i < (QR + 63) / 64; ++i) {
+        const int r = min(rs + i * 64 + lane, r_hi - 1);
+        const int t = g_pow2 ? r >> lg : r / a.G;
+        if (wave == 0) load_lds4(lbase, dst.lse + i * 64, (uint32_t)(t * a.Hq + (r - t * a.G)) * 4u);
+        else load_lds4(pbase, dst.pos + i * 64, (uint32_t)t * 4u);
       }
     }
   };
@@ -846,7 +1048,7 @@ __global__ __launch_bounds__(kThreads, (Occ<T, D>::value)) void colsum_kernel(P2
     }
   };
   // the sub-tile's LSE of this lane's rows (log2 units)
-  auto load_lv = [&](const QTile2<ROWB> &cur, int U, float (&lv)[16]) __attribute__((always_inline)) {
+  auto load_lv = [&](const QTile &cur, int U, float (&lv)[16]) __attribute__((always_inline)) {
 #pragma unroll
     for (int e4 = 0; e4 < 4; ++e4) {
       const float4 x = *reinterpret_cast<const float4 *>(&cur.lse[U * 32 + hi * 4 + 8 * e4]);
@@ -856,10 +1058,34 @@ __global__ __launch_bounds__(kThreads, (Occ<T, D>::value)) void colsum_kernel(P2
       lv[4 * e4 + 3] = x.w;
     }
   };
+  // fp32: this lane's operand rows of chain j on the rows from rsub on
+  auto fix_nan = [&](int j, int rsub) __attribute__((always_inline)) {
+    const int key = min(kw0 + j * 32 + col, L - 1);
+    replace_nan<D>(acc[j], qmem + row_off(rsub + col), a.k + ((size_t)(s0 + key) * a.Hkv + g) * ROWB, hi);
+  };
+  // fp32: chain j on the sub-tile in slot U, its fragments read PF k-steps ahead
+  auto split_chain = [&](const QTile &cur, int U, int j) __attribute__((always_inline)) {
+    constexpr int PF = 2;
+    frag f[NS];
+#pragma unroll
+    for (int s = 0; s < PF; ++s) f[s] = lds_frag<T, D>(cur.q, U * 32 + col, s * 2 * E + hi * E);
+#pragma unroll
+    for (int s = 0; s < NS; ++s) {
+      if (s + PF < NS) f[s + PF] = lds_frag<T, D>(cur.q, U * 32 + col, (s + PF) * 2 * E + hi * E);
+      acc[j] = MM::run(f[s], kf[j][s], acc[j]);
+    }
+    __builtin_amdgcn_sched_group_barrier(0x100, PF * MM::NP, 0);  // DS read
+#pragma unroll
+    for (int s = 0; s < NS; ++s) {
+      if (s + PF < NS) __builtin_amdgcn_sched_group_barrier(0x100, MM::NP, 0);
+      __builtin_amdgcn_sched_group_barrier(0x008, MM::NM, 0);  // MFMA
+    }
+  };
   // a sub-tile in stage slot U that every row of which sees every key of the
   // wave: chain j of MFMAs with the terms of chain j-DIST in between
-  auto sub_tile = [&](const QTile2<ROWB> &cur, auto u_tag, const frag (&av)[NS]) __attribute__((always_inline)) {
-    constexpr int U = decltype(u_tag)::value;
+  auto sub_tile = [&](const QTile &cur, auto u_tag, const frag (&av)[NS], int rsub)
+      __attribute__((always_inline)) {
+    const int U = u_tag;
     // this sub-tile's LSE, read once the pending chains no longer need plv
     float clv[16];
 #pragma unroll
@@ -878,9 +1104,20 @@ __global__ __launch_bounds__(kThreads, (Occ<T, D>::value)) void colsum_kernel(P2
         }
         interleave_mfma_valu<NS, (24 / NS > 0 ? 24 / NS : 1)>();
       } else {
+        if constexpr (SPLIT) {
+          split_chain(cur, U, j);
+        } else {
 #pragma unroll
-        for (int s = 0; s < NS; ++s) acc[j] = MM::run(av[s], kf[j][s], acc[j]);
+          for (int s = 0; s < NS; ++s) acc[j] = MM::run(av[s], kf[j][s], acc[j]);
+        }
         terms(pc, 0, 16, clv, ts);
+        if constexpr (SPLIT) {
+          const float t = ts[0] + ts[1];
+          if (__ballot(t != t) != 0ull) {
+            fix_nan(j, rsub);
+            terms(pc, 0, 16, clv, ts);
+          }
+        }
       }
       cs[pc] += ts[0] + ts[1];
     }
@@ -905,14 +1142,28 @@ __global__ __launch_bounds__(kThreads, (Occ<T, D>::value)) void colsum_kernel(P2
   // partial sums per chain, elements ascending) and a masked term is an
   // exact 0, so a key that sees every row of the sub-tile gets the same bits
   // on either path.
-  auto sub_masked = [&](const QTile2<ROWB> &cur, auto u_tag, const frag (&av)[NS]) __attribute__((always_inline)) {
-    constexpr int U = decltype(u_tag)::value;
+  auto sub_masked = [&](const QTile &cur, auto u_tag, const frag (&av)[NS], int rsub)
+      __attribute__((always_inline)) {
+    const int U = u_tag;
     settle();
 #pragma unroll
     for (int j = 0; j < NKT; ++j) {
       acc[j] = f32x16{};
+      if constexpr (SPLIT) {
+        split_chain(cur, U, j);
+      } else {
 #pragma unroll
-      for (int s = 0; s < NS; ++s) acc[j] = MM::run(av[s], kf[j][s], acc[j]);
+        for (int s = 0; s < NS; ++s) acc[j] = MM::run(av[s], kf[j][s], acc[j]);
+      }
+    }
+    if constexpr (SPLIT) {
+#pragma unroll
+      for (int j = 0; j < NKT; ++j) {
+        bool nan = false;
+#pragma unroll
+        for (int e = 0; e < 16; ++e) nan = nan || acc[j][e] != acc[j][e];
+        if (__ballot(nan) != 0ull) fix_nan(j, rsub);
+      }
     }
     float ts[NKT][2];
 #pragma unroll
@@ -939,34 +1190,60 @@ __global__ __launch_bounds__(kThreads, (Occ<T, D>::value)) void colsum_kernel(P2
   };
 
   const int nstage = (r_hi - r_lo + QR - 1) / QR;
-  if (nstage > 0) issue_stage(r_lo, qtA);
-  auto step = [&](QTile2<ROWB> &cur, QTile2<ROWB> &nxt, int st) __attribute__((always_inline)) {
+  if (nstage > 0) {
+    if constexpr (SPLIT) load_raw(r_lo);
+    issue_stage(r_lo, qtA);
+    if constexpr (SPLIT)
+      if (nstage > 1) load_raw(r_lo + QR);
+  }
+  auto step = [&](QTile &cur, QTile &nxt, int st) __attribute__((always_inline)) {
     const int rs = r_lo + st * QR;
     wait_vmem();
+    if (wave == 0 && rs + QR > r_hi) {  // (the wave that loaded the LSE)
+#pragma unroll
+      for (int i = 0; i < (QR + 63) / 64; ++i) {
+        const int r = i * 64 + lane;
+        if (r < QR && rs + r >= r_hi) cur.lse[r] = INFINITY;
+      }
+    }
     __syncthreads();  // stage st is in LDS; every wave is done with the other buffer
     if (st + 1 < nstage) issue_stage(rs + QR, nxt);
+    if constexpr (SPLIT)
+      if (st + 2 < nstage) load_raw(rs + 2 * QR);
     if (active) {
       auto one = [&](auto u_tag) __attribute__((always_inline)) {
-        constexpr int U = decltype(u_tag)::value;
+        const int U = u_tag;
         const int nv = min(32, r_hi - (rs + U * 32));  // valid rows of the sub-tile
         if (nv > 0) {
           // the query fragments are read together with the positions that
           // classify the sub-tile: one LDS round trip before the first MFMA
+          // (fp32: three times the registers, read by split_chain)
           frag av[NS];
 #pragma unroll
-          for (int s = 0; s < NS; ++s)
-            av[s] = load_frag<frag>(cur.q + swz_off<T, D>(U * 32 + col, s * 2 * E + hi * E));
+          for (int s = 0; s < (SPLIT ? 0 : NS); ++s)
+            av[s] = lds_frag<T, D>(cur.q, U * 32 + col, s * 2 * E + hi * E);
           const int qmin = cur.pos[U * 32], qmax = cur.pos[U * 32 + nv - 1];
           if (qmax >= kmin) {  // else no row of the sub-tile sees a key of the wave
-            if (qmin >= kmax) sub_tile(cur, u_tag, av);
-            else sub_masked(cur, u_tag, av);
+            if (qmin >= kmax) sub_tile(cur, u_tag, av, rs + U * 32);
+            else sub_masked(cur, u_tag, av, rs + U * 32);
           }
         }
       };
-      one(std::integral_constant<int, 0>{});
-      one(std::integral_constant<int, 1>{});
-      one(std::integral_constant<int, 2>{});
-      one(std::integral_constant<int, 3>{});
+      // One key tile per wave is the small-grid form: its few sub-tiles run
+      // in a rolled loop where fetching the unrolled code costs more than it
+      // saves (fp32, and d = 64: 3 sequences of 6 images 11.8 -> 11.3 us; bf16
+      // at d = 128 the other way, 8.0 -> 8.3 us at 4 x 729 tokens).
+      if constexpr (NKT == 1 && (SPLIT || D == 64)) {
+#pragma unroll 1
+        for (int U = 0; U < SUBS; ++U) one(U);
+      } else {
+        one(std::integral_constant<int, 0>{});
+        if constexpr (SUBS >= 2) one(std::integral_constant<int, 1>{});
+        if constexpr (SUBS == 4) {
+          one(std::integral_constant<int, 2>{});
+          one(std::integral_constant<int, 3>{});
+        }
+      }
     }
   };
   for (int st = 0; st < nstage; st += 2) {
@@ -1006,22 +1283,23 @@ hipError_t run_row_lse(hipStream_t st, const DevLayout &L, const AttnPlan &P, co
   a.part_l = (float *)(ws + P.off_part_l);
   const int nunits = L.B * Hkv * P.nkc;
   const int grid = ((nunits + 7) / 8) * 8 * P.nqb;
-  if (P.nt1 == 1)  // one query tile per wave on small grids (attn_plan)
-    hipLaunchKernelGGL((rowstats_kernel<T, D, 1>), dim3(grid), dim3(kThreads), 0, st, a);
-  else
-    hipLaunchKernelGGL((rowstats_kernel<T, D, kTiles1>), dim3(grid), dim3(kThreads), 0, st, a);
+  constexpr bool FP32 = Geo<T, D>::SPLIT;
+  if (P.nt1 == max_tiles1(FP32) && !P.small1)
+    hipLaunchKernelGGL((rowstats_kernel<T, D, max_tiles1(FP32), false>), dim3(grid), dim3(kThreads), 0, st, a);
+  else  // small grids (attn_plan)
+    hipLaunchKernelGGL((rowstats_kernel<T, D, 1, FP32>), dim3(grid), dim3(kThreads), 0, st, a);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   const int rows = Hq * L.T_tot;
   const dim3 cg((rows + 255) / 256), cb(256);
   if (P.nkc <= 8)
-    hipLaunchKernelGGL(lse_combine_kernel<8>, cg, cb, 0, st, a.part_m, a.part_l, rows, P.nkc,
+    hipLaunchKernelGGL(lse_combine_kernel<8>, cg, cb, 0, st, a.part_m, a.part_l, L.T_tot, Hq, P.nkc,
                        row_lse, lse2);
   else if (P.nkc <= 16)
-    hipLaunchKernelGGL(lse_combine_kernel<16>, cg, cb, 0, st, a.part_m, a.part_l, rows, P.nkc,
+    hipLaunchKernelGGL(lse_combine_kernel<16>, cg, cb, 0, st, a.part_m, a.part_l, L.T_tot, Hq, P.nkc,
                        row_lse, lse2);
   else
-    hipLaunchKernelGGL(lse_combine_kernel<32>, cg, cb, 0, st, a.part_m, a.part_l, rows, P.nkc,
+    hipLaunchKernelGGL(lse_combine_kernel<32>, cg, cb, 0, st, a.part_m, a.part_l, L.T_tot, Hq, P.nkc,
                        row_lse, lse2);
   return hipGetLastError();
 }
@@ -1050,17 +1328,14 @@ hipError_t run_colsum(hipStream_t st, const DevLayout &L, const AttnPlan &P, con
   a.ppx = (L.B * Hkv * P.nsl + 7) / 8;
   a.kps = (P.nkb + P.nsl - 1) / P.nsl;
   const int grid = 8 * a.ppx * a.kps * P.nqs;
-  if constexpr (Geo<T, D>::NT2 == 3) {  // narrower blocks for small grids (attn_plan)
-    if (P.nkt2 == 2) {
-      hipLaunchKernelGGL((colsum_kernel<T, D, 2>), dim3(grid), dim3(kThreads), 0, st, a);
-      return hipGetLastError();
-    }
-    if (P.nkt2 == 1) {
-      hipLaunchKernelGGL((colsum_kernel<T, D, 1>), dim3(grid), dim3(kThreads), 0, st, a);
-      return hipGetLastError();
-    }
-  }
-  hipLaunchKernelGGL((colsum_kernel<T, D, Geo<T, D>::NT2>), dim3(grid), dim3(kThreads), 0, st, a);
+  // narrower blocks for small grids (attn_plan)
+  constexpr int NT2 = Geo<T, D>::NT2;
+  if (P.nkt2 == NT2)
+    hipLaunchKernelGGL((colsum_kernel<T, D, NT2>), dim3(grid), dim3(kThreads), 0, st, a);
+  else if (P.nkt2 == 1)
+    hipLaunchKernelGGL((colsum_kernel<T, D, 1>), dim3(grid), dim3(kThreads), 0, st, a);
+  else if constexpr (NT2 > 2)
+    hipLaunchKernelGGL((colsum_kernel<T, D, 2>), dim3(grid), dim3(kThreads), 0, st, a);
   return hipGetLastError();
 }
 
@@ -1071,8 +1346,8 @@ inline size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 AttnPlan attn_plan(const DevLayout &L, int Hq, int Hkv, int d, int dtype) {
   AttnPlan P;
   P.G = Hq / Hkv;
-  const int row_bytes = d * (dtype == AVTP_FP32 ? 4 : 2);
-  int nkt2 = tiles_pass2(row_bytes);                            // pass 2 key tiles per wave
+  const bool fp32 = dtype == AVTP_FP32;
+  int nkt2 = tiles_pass2(d, fp32 ? 3 : 1);                      // pass 2 key tiles per wave
   P.rows_max = P.G * L.max_text;
   // Pass 1 geometry for nt query tiles per wave: query blocks per unit and
   // the key chunk.
@@ -1095,13 +1370,16 @@ AttnPlan attn_plan(const DevLayout &L, int Hq, int Hkv, int d, int dtype) {
       const long long two = (L.max_seqlen + 2 * kStage1 - 1) / (2 * kStage1);  // chunks of two stages
       kc = base * two < 256 ? (kc < kStage1 ? kStage1 : kc) : 2 * kStage1;
     }
+    // fp32 stages are shorter (24 KB of planes): there half a granule
+    if (fp32 && kc == kStage1 && base * ((L.max_seqlen + kc - 1) / kc) < 256) kc = kStage1 / 2;
     // Where that gives blocks of at most two stages but more than 512 of them
     // (more than one round at two blocks per CU), a block's fixed latency
     // (layout reads, query loads, the first stage's wait, the flush) outweighs
     // its work: take chunks long enough for at most 512 blocks, one round.
     // Two sequences of 8 images with 96 text rows: 1,024 blocks of two stages
     // -> 512 of four, pass 1 33.3 -> 28.8 us (384 or 256 blocks: 34.7, 29.7).
-    if (kc <= 2 * kStage1 && base <= 512 && base * ((L.max_seqlen + kc - 1) / kc) > 512) {
+    // (fp32 inputs have six times the work per stage: no such rule.)
+    if (!fp32 && kc <= 2 * kStage1 && base <= 512 && base * ((L.max_seqlen + kc - 1) / kc) > 512) {
       const long long per = 512 / base;  // chunks per unit
       long long k2 = (L.max_seqlen + per - 1) / per;
       k2 = ((k2 + kStage1 - 1) / kStage1) * kStage1;
@@ -1118,8 +1396,10 @@ AttnPlan attn_plan(const DevLayout &L, int Hq, int Hkv, int d, int dtype) {
   // images 127-131 -> 134-137 us, 4 x 32 images 536-540 -> 602-606 us).
   int nqb = 1;
   long long kc = 0;
-  P.nt1 = kTiles1;
-  if (pass1(kTiles1, nqb, kc) <= 512) {
+  P.nt1 = max_tiles1(fp32);
+  const long long blocks1 = pass1(P.nt1, nqb, kc);
+  P.small1 = fp32 && blocks1 < 256;
+  if (!fp32 && blocks1 <= 512) {
     P.nt1 = 1;
     pass1(1, nqb, kc);
   }
@@ -1127,22 +1407,24 @@ AttnPlan attn_plan(const DevLayout &L, int Hq, int Hkv, int d, int dtype) {
   P.kchunk = (int)kc;
   P.nkc = (L.max_seqlen + P.kchunk - 1) / P.kchunk;
   if (P.nkc < 1) P.nkc = 1;
-  // Pass 2: three key tiles per wave (384 keys per block) where that gives
+  // Pass 2: as many key tiles per wave as its registers hold (bf16: three at
+  // d = 128, 384 keys per block, four at d = 64) where that gives
   // at least 512 blocks; on smaller grids two, and one where two give fewer
   // than 256 blocks, so that more blocks share the chip (the rows a block
   // streams are the same whatever its width).  Two sequences of 8 images with
   // 96 text rows (336 -> 512 blocks): pass 2 34.5 -> 29.2 us; one sequence of
   // 4 x 729 tokens: 15.3 -> 12.8 (two tiles) -> 12.3 us (one).  At 2,432
   // blocks three tiles stay faster (8 x 16 images: 108-113 against 119-124).
+  // d = 64: 3 sequences of 6 images, 14 heads, 24 -> 180 blocks, 14.1 -> 11.3 us.
   auto key_blocks = [&](int nt) { return (L.max_seqlen + 4 * nt * 32 - 1) / (4 * nt * 32); };
   P.nkb = key_blocks(nkt2);
-  if (nkt2 == 3 && (long long)L.B * Hkv * P.nkb < 512) {
+  if (nkt2 > 2 && (long long)L.B * Hkv * P.nkb < 512) {
     nkt2 = 2;
     P.nkb = key_blocks(nkt2);
-    if ((long long)L.B * Hkv * P.nkb < 256) {
-      nkt2 = 1;
-      P.nkb = key_blocks(nkt2);
-    }
+  }
+  if (nkt2 > 1 && (long long)L.B * Hkv * P.nkb < 256) {
+    nkt2 = 1;
+    P.nkb = key_blocks(nkt2);
   }
   if (P.nkb < 1) P.nkb = 1;
   P.nkt2 = nkt2;
@@ -1175,8 +1457,6 @@ AttnPlan attn_plan(const DevLayout &L, int Hq, int Hkv, int d, int dtype) {
   off = align256(off + sizeof(float) * rows * P.nkc);
   P.off_part_l = off;
   off = align256(off + sizeof(float) * rows * P.nkc);
-  P.off_lse = off;
-  off = align256(off + sizeof(float) * rows);
   P.off_lse2 = off;
   off = align256(off + sizeof(float) * rows);
   P.off_colsum = off;
@@ -1196,10 +1476,12 @@ hipError_t launch_row_lse(hipStream_t st, const DevLayout &L, const AttnPlan &P,
                   : run_row_lse<float, 64>(st, L, P, q, k, Hq, Hkv, scale, row_lse, lse2, ws);
 }
 
-hipError_t launch_lse_to_log2(hipStream_t st, int rows, const float *lse, float *lse2) {
+hipError_t launch_lse_to_log2(hipStream_t st, int T_tot, int Hq, const float *lse, float *lse2) {
   clear_pending_error();
+  const int rows = T_tot * Hq;
   if (rows <= 0) return hipSuccess;
-  hipLaunchKernelGGL(lse_to_log2_kernel, dim3((rows + 255) / 256), dim3(256), 0, st, lse, rows, lse2);
+  hipLaunchKernelGGL(lse_to_log2_kernel, dim3((rows + 255) / 256), dim3(256), 0, st, lse, T_tot, Hq,
+                     lse2);
   return hipGetLastError();
 }
 

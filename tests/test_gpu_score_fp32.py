@@ -1,0 +1,67 @@
+"""fp32 attention scores on the split bf16 MFMA path: stage and tile edges
+against the float64 oracle, and infinite inputs whose logits are -inf."""
+import numpy as np
+import pytest
+import torch
+
+from gpu_util import TOL, need_gpu, say
+from oracle import avtp_oracle as O
+from paper_2608_26806_amd import avtp as A
+from paper_2608_26806_amd.workloads import build_layout
+
+pytestmark = pytest.mark.gpu
+
+# head size, query heads, key heads, images, text before each, text at the end.
+# Stages are 32 (d = 128) or 64 (d = 64) rows of 32-row tiles; key blocks are
+# 128 or 256 keys; one to several sequences and query rows per key head.
+CASES = [
+    (128, 1, 1, [[31]], 0, 1), (128, 4, 2, [[32], [33]], 0, 8), (128, 3, 1, [[63, 65], [1]], 1, 10),
+    (128, 8, 4, [[127, 129, 128]], 3, 17), (64, 2, 1, [[63]], 0, 16), (64, 7, 1, [[64, 65]], 1, 9),
+    (64, 4, 4, [[255, 257], [513]], 2, 33), (64, 8, 2, [[700, 900], [31, 1]], 5, 64),
+]
+
+
+def _draw(case, seed):
+    d, Hq, Hkv, imgs, pre, tail = case
+    lay = build_layout(imgs, pre, tail, 50)
+    rng = np.random.default_rng(seed)
+    q = rng.standard_normal((lay.T_tot, Hq, d), dtype=np.float32)
+    k = rng.standard_normal((lay.N_tok, Hkv, d), dtype=np.float32) * np.exp(
+        0.5 * rng.standard_normal((lay.N_tok, 1, 1))).astype(np.float32)
+    return lay, q, k
+
+
+@pytest.mark.parametrize("case", CASES, ids=lambda c: f"d{c[0]}h{c[1]}-{c[2]}i{c[3]}t{c[4]}-{c[5]}")
+def test_scores_match_the_oracle_at_the_edges(case):
+    need_gpu()
+    say(f"fp32 scores {case}")
+    lay, q, k = _draw(case, 11)
+    d, Hq, Hkv = case[:3]
+    dl = A.DeviceLayout(lay)
+    s, isum = A.score_attn(dl, torch.from_numpy(q).cuda(), torch.from_numpy(k).cuda(), d ** -0.5)
+    s_o, isum_o, _, _ = O.attn_scores(lay, q, k, Hq, Hkv, d ** -0.5, "fp32")
+    vis = lay.visual_mask()
+    np.testing.assert_allclose(s.cpu().numpy()[vis], s_o[vis], rtol=TOL["fp32"])
+    np.testing.assert_allclose(isum.cpu().numpy(), isum_o, rtol=TOL["fp32"])
+
+
+@pytest.mark.parametrize("d", [64, 128])
+def test_an_infinite_key_value_with_negative_logits(d):
+    """A key whose logits are all -inf scores 0 and leaves the others as they
+    are without it (the split products of an infinity are not numbers)."""
+    need_gpu()
+    say(f"fp32 scores, infinite key value, d={d}")
+    lay, q, k = _draw((d, 4, 2, [[200, 100]], 2, 20), 5)
+    q[:, :, 3] = -np.abs(q[:, :, 3]) - 0.1
+    j = int(lay.img_start[0]) + 40
+    k[j, :, 3] = np.inf
+    dl = A.DeviceLayout(lay)
+    s, isum = A.score_attn(dl, torch.from_numpy(q).cuda(), torch.from_numpy(k).cuda(), d ** -0.5)
+    s, vis = s.cpu().numpy(), lay.visual_mask()
+    kk = k.copy()
+    kk[j] = 0.0
+    kk[j, :, 3] = 1e6  # its logits below -1000: the same zero weight, in finite numbers
+    s_o, _, _, _ = O.attn_scores(lay, q, kk, 4, 2, d ** -0.5, "fp32")
+    assert s[j] == 0.0
+    vis[j] = False
+    np.testing.assert_allclose(s[vis], s_o[vis], rtol=TOL["fp32"])
