@@ -179,11 +179,7 @@ class DeviceLayout:
         self.N_tok = int(h["cu_seqlens"][-1]) if self.B >= 0 and len(h["cu_seqlens"]) else 0
         self.T_tot = len(h["text_pos"])
         self.N_out = int(self.T_tot + int(np.sum(h["keep_total"], dtype=np.int64)))
-        # one device buffer holds every array (a zero-length array still gets a valid pointer)
-        offs, tot = {}, 0
-        for n in self.NAMES:
-            offs[n] = tot
-            tot += max(1, len(h[n]))
+        offs, tot = self._offsets({n: len(h[n]) for n in self.NAMES})
         flat = np.zeros(tot, dtype=np.int32)
         for n in self.NAMES:
             flat[offs[n]:offs[n] + len(h[n])] = h[n]
@@ -191,10 +187,48 @@ class DeviceLayout:
             self.dev = torch.from_numpy(flat)
         else:
             self.dev = torch.from_numpy(flat).to(device)
-        base, es = self.dev.data_ptr(), 4
+        self._point(offs)
+
+    @classmethod
+    def _offsets(cls, lens):
+        """Where each array starts in the one device buffer that holds them
+        all (a zero-length array still gets a valid pointer), and its length."""
+        offs, tot = {}, 0
+        for n in cls.NAMES:
+            offs[n] = tot
+            tot += max(1, lens[n])
+        return offs, tot
+
+    def _point(self, offs):
+        h, base, es = self.host, self.dev.data_ptr(), 4
         self.st = _Layout(self.B, self.n_img, self.N_tok, self.T_tot,
                           *[base + es * offs[n] for n in self.NAMES],
                           *[h[n].ctypes.data for n in self.NAMES])
+
+    @classmethod
+    def pruned(cls, dl: "DeviceLayout", keep_idx: torch.Tensor, cu_out: torch.Tensor, keep_totals,
+               stream=None) -> "DeviceLayout":
+        """The layout of the tokens that a selection on ``dl`` kept: the arrays
+        of ``pruned_layout``, written where the new layout holds them and
+        copied to the host in one piece (one synchronisation of torch's current
+        stream).  keep_totals(img_len, cu_img) gives its keep totals."""
+        lens = {"cu_seqlens": dl.B + 1, "img_start": dl.n_img, "img_len": dl.n_img,
+                "cu_img": dl.B + 1, "text_pos": dl.T_tot, "cu_text": dl.B + 1, "keep_total": dl.B}
+        offs, tot = cls._offsets(lens)
+        self = cls.__new__(cls)
+        self.dev = torch.empty(tot, dtype=torch.int32, device=cu_out.device)
+        pruned_layout(dl, keep_idx, cu_out, stream=stream,
+                      out={n: self.dev[offs[n]:offs[n] + max(1, lens[n])] for n in cls.NAMES[:-1]})
+        k0 = offs["keep_total"]
+        flat = self.dev[:k0].cpu().numpy()
+        h = self.host = {n: flat[offs[n]:offs[n] + lens[n]] for n in cls.NAMES[:-1]}
+        h["keep_total"] = np.ascontiguousarray(keep_totals(h["img_len"], h["cu_img"]), dtype=np.int32)
+        self.dev[k0:].copy_(torch.from_numpy(h["keep_total"]))
+        self.B, self.n_img, self.T_tot = dl.B, dl.n_img, dl.T_tot
+        self.N_tok = int(h["cu_seqlens"][-1])
+        self.N_out = int(self.T_tot + int(np.sum(h["keep_total"], dtype=np.int64)))
+        self._point(offs)
+        return self
 
     def ref(self):
         return ctypes.byref(self.st)

@@ -27,8 +27,9 @@ from . import avtp as A
 
 def keep_totals(img_len: np.ndarray, cu_img: np.ndarray, keep_pct: int) -> np.ndarray:
     """keep_total[b] = round-half-up(keep_pct % of sequence b's visual tokens)."""
-    return np.array([(keep_pct * int(np.sum(img_len[cu_img[b]:cu_img[b + 1]], dtype=np.int64)) + 50)
-                     // 100 for b in range(len(cu_img) - 1)], dtype=np.int32)
+    before = np.concatenate(([0], np.cumsum(img_len, dtype=np.int64)))
+    cu = np.asarray(cu_img)
+    return ((keep_pct * (before[cu[1:]] - before[cu[:-1]]) + 50) // 100).astype(np.int32)
 
 
 class ProgressivePruner:
@@ -55,13 +56,15 @@ class ProgressivePruner:
         keep_pct_next) and self.h_prior is h_out."""
         dl = self.dl
         scores, isum = A.score_variation(dl, h_cur, self.h_prior, status=status)
-        bud = A.budget(dl, isum, self.alpha, self.lo, self.hi, self.floor, mode=self.mode,
-                       status=status)
-        keep, cu_out = A.select(dl, scores, bud, status=status)
-        outs = A.compact_new(dl, keep, [(h_cur, 0), *others])
-        arrays = A.pruned_layout(dl, keep, cu_out)
-        host = {n: t.cpu().numpy() for n, t in arrays.items()}     # one sync per pruning layer
-        host["keep_total"] = keep_totals(host["img_len"], host["cu_img"], keep_pct_next)
-        self.dl = A.DeviceLayout(host, device=h_cur.device)
-        self.h_prior = outs[0]
-        return outs[0], outs[1:], keep[: dl.N_out], bud, scores, isum
+        pairs = []
+        for src, tdim in [(h_cur, 0), *others]:
+            shape = list(src.shape)
+            shape[tdim] = dl.N_out
+            pairs.append((src, torch.empty(shape, dtype=src.dtype, device=src.device), tdim))
+        bud, keep, cu_out = A.budget_select_compact(dl, isum, scores, pairs, self.alpha, self.lo, self.hi,
+                                                    self.floor, mode=self.mode, status=status)
+        # (one synchronisation per pruning layer)
+        self.dl = A.DeviceLayout.pruned(dl, keep, cu_out,
+                                        lambda n, cu: keep_totals(n, cu, keep_pct_next))
+        self.h_prior = pairs[0][1]
+        return pairs[0][1], [p[1] for p in pairs[1:]], keep, bud, scores, isum
