@@ -389,8 +389,8 @@ __global__ __launch_bounds__(kThreads) void select_kernel(SelArgs A, RuleArgs R,
 // Fused selection and compaction: S blocks per image (slices).  Every slice
 // runs the image's selection (its keys are few and sit in LDS), owns the
 // output rows o with o mod S == slice, writes their keep_idx entries, lists
-// them in LDS, and then copies those rows of every tensor with groups of
-// lanes.  No block waits for another.
+// them in LDS, and then copies those rows of every tensor as one run of
+// vector units.  No block waits for another.
 constexpr int kListCap = 4096;  // output rows one slice may own (the host sizes S for it)
 
 struct SCArgs {
@@ -401,29 +401,88 @@ struct SCArgs {
   int32_t *status;
   int S;
   int n_t;
+  uint32_t row_units;                     // vector units of one row of every tensor
+  uint32_t unit_begin[AVTP_MAX_TENSORS];  // and of the tensors before each
   CTensor t[AVTP_MAX_TENSORS];
 };
 
-// The listed rows of one tensor, a power-of-two group of lanes per row (as in
-// the compaction kernel), four rows per group at once.
-template <typename V>
-__device__ inline void copy_listed(const CTensor &T, const int *lo, const int *lj, int n) {
-  const int lpr_shift = T.lpr_shift;
-  const int lane = threadIdx.x & ((1 << lpr_shift) - 1);
-  const int per_pass = kThreads >> lpr_shift;
-  for (int p = 0; p < T.planes; ++p)
-    copy_rows_batched<V, false>(T, p, (long long)(threadIdx.x >> lpr_shift), n, per_pass, lane,
-                         [&](long long e, long long &j, long long &r) __attribute__((always_inline)) {
-                           j = lj[e];
-                           r = lo[e];
-                           return true;
-                         });
+// One vector unit of one row of one tensor on its way through a register.
+struct UnitJob {
+  const char *s;
+  char *d;
+  int vshift;  // -1: none
+  uint4 v;
+  __device__ inline void load() {
+    switch (vshift) {
+      case 4: v = *reinterpret_cast<const uint4 *>(s); break;
+      case 3: {
+        const uint2 x = *reinterpret_cast<const uint2 *>(s);
+        v.x = x.x;
+        v.y = x.y;
+        break;
+      }
+      case 2: v.x = *reinterpret_cast<const uint32_t *>(s); break;
+      case 1: v.x = *reinterpret_cast<const uint16_t *>(s); break;
+      case 0: v.x = *reinterpret_cast<const uint8_t *>(s); break;
+      default: break;
+    }
+  }
+  __device__ inline void store() const {
+    switch (vshift) {
+      case 4: *reinterpret_cast<uint4 *>(d) = v; break;
+      case 3: *reinterpret_cast<uint2 *>(d) = make_uint2(v.x, v.y); break;
+      case 2: *reinterpret_cast<uint32_t *>(d) = v.x; break;
+      case 1: *reinterpret_cast<uint16_t *>(d) = (uint16_t)v.x; break;
+      case 0: *reinterpret_cast<uint8_t *>(d) = (uint8_t)v.x; break;
+      default: break;
+    }
+  }
+};
+
+// The listed rows of every tensor, as one run of vector units: a block has few
+// rows (4 MiB over about 1024 blocks), so what counts is that all its loads are
+// in flight at once, two per thread at a time.  One tensor after the other, a
+// round of memory latency each, the call took 10.6 us at 2 x 64 tokens with
+// hidden states, positions, K and V; as one run 9.1.
+__device__ inline void copy_listed(const CTensor *t, const uint32_t *unit_begin, int n_t,
+                                   uint32_t row_units, const int *lo, const int *lj, int n) {
+  const uint32_t total = (uint32_t)n * row_units;
+  auto job = [&](uint32_t x) __attribute__((always_inline)) {
+    UnitJob w;
+    w.vshift = -1;
+    w.v = make_uint4(0, 0, 0, 0);
+    if (x < total) {
+      const uint32_t e = x / row_units, y = x - e * row_units;
+      int ti = 0;
+      while (ti + 1 < n_t && y >= unit_begin[ti + 1]) ++ti;
+      const CTensor &T = t[ti];
+      const uint32_t z = y - unit_begin[ti], units = (uint32_t)T.units;
+      const uint32_t p = T.planes > 1 ? z / units : 0, u = z - p * units;
+      w.vshift = T.vshift;
+      w.s = T.src + p * T.src_plane_stride + lj[e] * T.src_stride + ((long long)u << T.vshift);
+      w.d = T.dst + p * T.dst_plane_stride + lo[e] * T.dst_stride + ((long long)u << T.vshift);
+    }
+    return w;
+  };
+  for (uint32_t x = threadIdx.x; x < total; x += 2 * kThreads) {
+    UnitJob a = job(x), b = job(x + kThreads);
+    a.load();
+    b.load();
+    a.store();
+    b.store();
+  }
 }
 
 template <int MODE>
 __global__ __launch_bounds__(kThreads) void select_compact_kernel(SCArgs a, RuleArgs R) {
   __shared__ int list_o[kListCap], list_j[kListCap];
   __shared__ int list_n;
+  __shared__ CTensor tensors[AVTP_MAX_TENSORS];  // (indexed per thread by the copy)
+  __shared__ uint32_t unit_begin[AVTP_MAX_TENSORS];
+  if ((int)threadIdx.x < a.n_t) {
+    tensors[threadIdx.x] = a.t[threadIdx.x];
+    unit_begin[threadIdx.x] = a.unit_begin[threadIdx.x];
+  }
   const int S = a.S;
   const int img = (int)blockIdx.x / S, sl = (int)blockIdx.x - img * S;
   if (threadIdx.x == 0) list_n = 0;
@@ -431,7 +490,7 @@ __global__ __launch_bounds__(kThreads) void select_compact_kernel(SCArgs a, Rule
   SelArgs A = a.sel;
   if (sl != 0) A.cu_out = nullptr;
   auto put = [&](long long o, int32_t v, int seq) __attribute__((always_inline)) {
-    if ((int)(o % S) != sl) return;
+    if ((uint32_t)o % (uint32_t)S != (uint32_t)sl) return;  // (o < 2^31: N_tok is an int)
     if (o >= a.cap) {
       if (a.status) atomicOr(a.status + seq, AVTP_FLAG_OUT_CAPACITY);
       return;
@@ -448,17 +507,7 @@ __global__ __launch_bounds__(kThreads) void select_compact_kernel(SCArgs a, Rule
   };
   select_image<MODE>(A, R, img, sl == 0, a.status, put);
   __syncthreads();
-  const int n = min(list_n, kListCap);
-  for (int ti = 0; ti < a.n_t; ++ti) {
-    const CTensor &T = a.t[ti];
-    switch (T.vshift) {
-      case 4: copy_listed<uint4>(T, list_o, list_j, n); break;
-      case 3: copy_listed<uint2>(T, list_o, list_j, n); break;
-      case 2: copy_listed<uint32_t>(T, list_o, list_j, n); break;
-      case 1: copy_listed<uint16_t>(T, list_o, list_j, n); break;
-      default: copy_listed<uint8_t>(T, list_o, list_j, n); break;
-    }
-  }
+  copy_listed(tensors, unit_begin, a.n_t, a.row_units, list_o, list_j, min(list_n, kListCap));
 }
 
 // Blocks per image of the one-launch selection + compaction: about 1024
@@ -487,7 +536,12 @@ static SCArgs sc_args(const DevLayout &L, const float *scores, const int32_t *bu
   a.n_out = n_out;
   a.status = status;
   a.n_t = n_tensors;
-  for (int i = 0; i < n_tensors; ++i) describe_tensor(tensors[i], kThreads, a.t[i]);
+  a.row_units = 0;
+  for (int i = 0; i < n_tensors; ++i) {
+    describe_tensor(tensors[i], kThreads, a.t[i]);
+    a.unit_begin[i] = a.row_units;
+    a.row_units += (uint32_t)a.t[i].units * (uint32_t)a.t[i].planes;
+  }
   a.S = compact_slices(L);
   return a;
 }
