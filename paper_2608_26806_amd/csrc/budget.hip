@@ -23,9 +23,10 @@ __global__ __launch_bounds__(NTH) void budget_kernel(const float *__restrict__ i
                                                      int floor_abs, int32_t *__restrict__ budget,
                                                      int32_t *__restrict__ status) {
   const int b = blockIdx.x;
-  int32_t *out = budget + cu_img[b];
-  budget_rule::seq_budget<NTH>(b, img_sum, img_len, cu_img, keep_total, mode, alpha, lo_pm, hi_pm,
-                               floor_abs, status,
+  const int i0 = cu_img[b];
+  int32_t *out = budget + i0;
+  budget_rule::seq_budget<NTH>(b, i0, cu_img[b + 1] - i0, img_sum, img_len, keep_total, mode, alpha,
+                               lo_pm, hi_pm, floor_abs, status,
                                [&](int t, int32_t v) __attribute__((always_inline)) { out[t] = v; });
 }
 

@@ -177,16 +177,16 @@ __device__ inline Frac2 frac_ext_combine(const Frac2 &a, const Frac2 &b) {
   return r;
 }
 
-// The budgets of sequence b's images, by a block of NTH threads (every
-// thread of the block calls it; b is block-uniform).  The thread of image
+// The budgets of sequence b's images (m of them, from image i0 on), by a block
+// of NTH threads (every thread of the block calls it; b is block-uniform).  The thread of image
 // i0 + t calls out(t, budget) once, t < the sequence's image count; a
 // sequence without images calls nothing.  Sets AVTP_FLAG_INFEASIBLE in
 // status[b] (if status is given) when keep_total[b] is outside the bounds.
 template <int NTH, typename Out>
 __device__ __attribute__((always_inline)) inline void seq_budget(
-    int b, const float *__restrict__ img_sum, const int32_t *__restrict__ img_len,
-    const int32_t *__restrict__ cu_img, const int32_t *__restrict__ keep_total, int mode,
-    float alpha, int lo_pm, int hi_pm, int floor_abs, int32_t *__restrict__ status, Out out) {
+    int b, int i0, int m, const float *__restrict__ img_sum, const int32_t *__restrict__ img_len,
+    const int32_t *__restrict__ keep_total, int mode, float alpha, int lo_pm, int hi_pm,
+    int floor_abs, int32_t *__restrict__ status, Out out) {
   __shared__ uint32_t W[kMaxImg], lo[kMaxImg], hi[kMaxImg];
   __shared__ uint64_t rem[kMaxImg];
   __shared__ uint64_t fpart[NTH];  // partial f of a breakpoint, one per thread
@@ -198,7 +198,6 @@ __device__ __attribute__((always_inline)) inline void seq_budget(
   __shared__ double sh_S, red_d[4];
 
   const int tid = threadIdx.x;
-  const int i0 = cu_img[b], m = cu_img[b + 1] - i0;
   const long long K = keep_total[b];
   if (m <= 0) return;
   const bool mine = tid < m;  // this thread's image is tid
