@@ -206,18 +206,21 @@ class DeviceLayout:
                           *[h[n].ctypes.data for n in self.NAMES])
 
     @classmethod
-    def pruned(cls, dl: "DeviceLayout", keep_idx: torch.Tensor, cu_out: torch.Tensor, keep_totals,
-               stream=None) -> "DeviceLayout":
+    def pruned(cls, dl: "DeviceLayout", keep_idx: torch.Tensor, cu_out: torch.Tensor,
+               keep_totals) -> "DeviceLayout":
         """The layout of the tokens that a selection on ``dl`` kept: the arrays
         of ``pruned_layout``, written where the new layout holds them and
-        copied to the host in one piece (one synchronisation of torch's current
-        stream).  keep_totals(img_len, cu_img) gives its keep totals."""
+        copied to the host in one piece (one synchronisation).  All of it runs
+        on torch's current stream: the buffer's allocation, the kernel, the
+        copy to the host and the upload of the keep totals depend on each other,
+        so a caller with another stream enters torch.cuda.stream(s) first.
+        keep_totals(img_len, cu_img) gives the new layout's keep totals."""
         lens = {"cu_seqlens": dl.B + 1, "img_start": dl.n_img, "img_len": dl.n_img,
                 "cu_img": dl.B + 1, "text_pos": dl.T_tot, "cu_text": dl.B + 1, "keep_total": dl.B}
         offs, tot = cls._offsets(lens)
         self = cls.__new__(cls)
         self.dev = torch.empty(tot, dtype=torch.int32, device=cu_out.device)
-        pruned_layout(dl, keep_idx, cu_out, stream=stream,
+        pruned_layout(dl, keep_idx, cu_out,
                       out={n: self.dev[offs[n]:offs[n] + max(1, lens[n])] for n in cls.NAMES[:-1]})
         k0 = offs["keep_total"]
         flat = self.dev[:k0].cpu().numpy()

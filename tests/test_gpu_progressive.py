@@ -120,3 +120,29 @@ def test_three_pruning_layers_match_oracle_stage_by_stage(dtype):
         assert pruner.dl.host["img_len"].tolist() == bud_h.tolist()
         pos = pos_out
         cur_lay = nxt
+
+
+def test_the_next_layout_under_another_current_stream():
+    """DeviceLayout.pruned under torch.cuda.stream(s): its host arrays are those
+    of the selection that is still queued on s."""
+    imgs, pre, tail = LAYOUTS["mixed"]
+    lay = build_layout(imgs, pre, tail, 50)
+    say("pruned layout under another stream")
+    keep, cu = _random_keep(lay, np.random.default_rng(3))
+    ref = O.pruned_layout(lay, keep, cu, np.zeros(lay.B, np.int32))
+    dl = A.DeviceLayout(lay)
+    keep_d, cu_d = torch.from_numpy(keep).cuda(), torch.from_numpy(cu).cuda()
+    w = torch.randn(4096, 4096, device="cuda")
+    s = torch.cuda.Stream()
+    s.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(s):
+        late_keep, late_cu = torch.zeros_like(keep_d), torch.zeros_like(cu_d)
+        for _ in range(8):          # the selection's outputs arrive after this work
+            w = w @ w * 1e-2
+        late_keep.copy_(keep_d)
+        late_cu.copy_(cu_d)
+        got = A.DeviceLayout.pruned(dl, late_keep, late_cu, lambda n, c: np.zeros(lay.B, np.int32))
+    torch.cuda.synchronize()
+    for n in A.DeviceLayout.NAMES[:-1]:
+        assert got.host[n].tolist() == getattr(ref, n).tolist(), n
+        assert got.device_array(n).tolist() == getattr(ref, n).tolist(), n
