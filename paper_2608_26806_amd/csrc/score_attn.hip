@@ -621,12 +621,18 @@ __global__ __launch_bounds__(kThreads, kWavesPerSimd) void rowstats_kernel(P1Arg
     if (__ballot(bad) != 0ull) {
       if constexpr (SPLIT) {
 #pragma unroll
-        for (int qi = 0; qi < NT; ++qi)
-          if (__ballot(t[qi] != t[qi]) != 0ull) {
+        for (int qi = 0; qi < NT; ++qi) {
+          // (a sum alone does not tell: a lane that sees none of the tile and
+          // has no reference yet sums exp2(-inf + inf))
+          bool nan = false;
+#pragma unroll
+          for (int e = 0; e < 16; ++e) nan = nan || (eoff(e) <= vl[qi] && acc[PS + qi][e] != acc[PS + qi][e]);
+          if (__ballot(nan) != 0ull) {
             const int row = min(wr0 + qi * 32 + col, R - 1), tk = row / a.G;
             replace_nan<D>(acc[PS + qi], kmem + (size_t)min(pend_kb + col, kend - 1) * kstride,
                            a.q + ((size_t)(t0 + tk) * a.Hq + g * a.G + (row - tk * a.G)) * ROWB, hi);
           }
+        }
       }
       // exact redo of the chains whose sum left the range: raise the
       // reference to the chain's maximum and rescale the row sum

@@ -65,3 +65,43 @@ def test_an_infinite_key_value_with_negative_logits(d):
     assert s[j] == 0.0
     vis[j] = False
     np.testing.assert_allclose(s[vis], s_o[vis], rtol=TOL["fp32"])
+
+
+@pytest.mark.parametrize("d", [64, 128])
+def test_partly_filled_row_tiles_cost_no_more_than_full_ones(d):
+    """40 query rows per key head (a full row tile and one of 8 rows) against 64
+    (two full tiles) over the same keys: the same tiles, so not slower.  The
+    unused rows see no key, and must not send finite inputs to the fp32 MFMA
+    (with that every tile of such a wave waits for d / 2 memory round trips:
+    2 to 4 times the time)."""
+    need_gpu()
+    say(f"fp32 row tiles, d={d}")
+
+    def call(rows):
+        lay, q, k = _draw((d, 4, 1, [[1024, 1000]], 0, rows // 4), 3)
+        dl = A.DeviceLayout(lay)
+        q, k = torch.from_numpy(q).cuda(), torch.from_numpy(k).cuda()
+        out = torch.empty(4, lay.T_tot, device="cuda")
+        ws = A.alloc_workspace(A.score_workspace_bytes(dl, A.SCORE_ATTN, A.FP32, 4, 1, d))
+        A.row_lse(dl, q, k, d ** -0.5, out=out, ws=ws)
+        torch.cuda.synchronize()
+        g = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(g):               # (the call's host part is as long as its kernels)
+            for _ in range(20):
+                A.row_lse(dl, q, k, d ** -0.5, out=out, ws=ws)
+        return g, (dl, q, k, out, ws)
+
+    def us(g):
+        a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        a.record()
+        g.replay()
+        b.record()
+        b.synchronize()
+        return a.elapsed_time(b) * 50
+
+    (part, _keep0), (full, _keep1) = call(40), call(64)
+    us(part), us(full)
+    t_part, t_full = min(us(part) for _ in range(9)), min(us(full) for _ in range(9))
+    say(f"40 rows {t_part:.1f} us, 64 rows {t_full:.1f} us")
+    # the best of nine runs of 20 calls varies by a few per cent
+    assert t_part < 1.25 * t_full
