@@ -63,7 +63,7 @@ struct Mma<__bf16> {
 };
 // fp32 inputs run on the bf16 MFMA too, 16 times the rate of the fp32 one: a
 // value is the sum of three bf16 numbers (8 bits each, remainders taken
-// exactly, so 2^-25 of the value or less is lost) and a product is the six
+// exactly: nothing is lost above 2^-109, see split8) and a product is the six
 // partial products down to 2^-16 of it, smallest first; those left out are
 // below 2^-24 of it, the fp32 rounding.  A chain has 48 fp32 accumulations at
 // d = 128 where the fp32 MFMA has 64: the scores' error against 64 bits is the
@@ -88,9 +88,15 @@ struct Mma<float> {
 };
 
 // Eight fp32 values as three bf16 planes (nearest even; remainders exact).
-__device__ inline Mma<float>::frag split8(const float4 &u, const float4 &v) {
+// Of a value below about 2^-109 the third part is below bf16's smallest step.
+// What it loses, 2^-126 at most, only matters next to a value of `big` or more
+// (split_big): a row that holds one gets a part that is not a number, so that
+// its elements come from the fp32 MFMA (replace_nan).  3 instructions per 4
+// values on top of about 22.
+__device__ inline Mma<float>::frag split8(const float4 &u, const float4 &v, float big) {
   const float x[8] = {u.x, u.y, u.z, u.w, v.x, v.y, v.z, v.w};
   Mma<float>::frag f;
+  float rest[8], top = 0.f;
 #pragma unroll
   for (int i = 0; i < 8; ++i) {
     const __bf16 h = (__bf16)x[i];
@@ -98,10 +104,18 @@ __device__ inline Mma<float>::frag split8(const float4 &u, const float4 &v) {
     const __bf16 m = (__bf16)r;
     f.p[0][i] = h;
     f.p[1][i] = m;
-    f.p[2][i] = (__bf16)(r - (float)m);
+    rest[i] = r - (float)m;
+    top = __builtin_fmaxf(top, __builtin_fabsf(x[i]));
   }
+  rest[0] = top < big ? rest[0] : NAN;
+#pragma unroll
+  for (int i = 0; i < 8; ++i) f.p[2][i] = (__bf16)rest[i];
   return f;
 }
+// The least value next to which a lost 2^-126 shows: 2 d products of it are
+// 2^-25 of a logit's log2 units, below the rounding of the exp2 argument.
+// (Infinite for a tiny scale: no value matters then.)
+inline float split_big(int d, float cl2e) { return 6.338253e29f / ((float)d * cl2e); }  // 2^99
 
 // fp32 inputs: replace the elements of a 32x32 tile that are not a number by
 // the fp32 MFMA's, `a` and `b` being this lane's operand rows in memory (row
@@ -178,9 +192,9 @@ __device__ inline typename Mma<T>::frag lds_frag(const char *stage, int row, int
 }
 // the operand elements at p in memory
 template <typename T>
-__device__ inline typename Mma<T>::frag mem_frag(const char *p) {
+__device__ inline typename Mma<T>::frag mem_frag(const char *p, float big) {
   if constexpr (Mma<T>::NP > 1)
-    return split8(load_frag<float4>(p), load_frag<float4>(p + 16));
+    return split8(load_frag<float4>(p), load_frag<float4>(p + 16), big);
   else
     return load_frag<bf16x8>(p);
 }
@@ -205,11 +219,11 @@ struct SplitStage {
       hi[i] = load_frag<float4>(p + 16);
     }
   }
-  __device__ inline void store(char *stage, int tid) const {
+  __device__ inline void store(char *stage, int tid, float big) const {
 #pragma unroll
     for (int i = 0; i < UPT; ++i) {
       const int u = tid + i * kThreads;
-      const Mma<float>::frag f = split8(lo[i], hi[i]);
+      const Mma<float>::frag f = split8(lo[i], hi[i], big);
       char *p = stage + swz_off<float, D>(u / UPR, (u % UPR) * 8);
 #pragma unroll
       for (int q = 0; q < 3; ++q) *reinterpret_cast<bf16x8 *>(p + q * G_::STAGE * G_::PROWB) = f.p[q];
@@ -388,7 +402,7 @@ struct P1Args {
   const int32_t *cu_seqlens, *cu_text, *text_pos;
   int B, Hq, Hkv, G, T_tot;
   int nqb, nkc, kchunk;
-  float cl2e;
+  float cl2e, big;  // big: fp32 inputs, see split8
   float *part_m, *part_l;  // [nkc][T_tot][Hq]
 };
 
@@ -513,7 +527,7 @@ __global__ __launch_bounds__(kThreads, kWavesPerSimd) void rowstats_kernel(P1Arg
       qrel[i] = tp[t] - s0;
       const char *src = a.q + ((size_t)(t0 + t) * a.Hq + h) * ROWB + hi * E * sizeof(T);
 #pragma unroll
-      for (int s = 0; s < NS; ++s) qf[i][s] = mem_frag<T>(src + s * 2 * E * sizeof(T));
+      for (int s = 0; s < NS; ++s) qf[i][s] = mem_frag<T>(src + s * 2 * E * sizeof(T), a.big);
     } else {
 #pragma unroll
       for (int s = 0; s < NS; ++s) qf[i][s] = frag{};
@@ -677,7 +691,7 @@ __global__ __launch_bounds__(kThreads, kWavesPerSimd) void rowstats_kernel(P1Arg
   const int kw_end = active ? min(kstop, wmax - s0 + 1) : kbeg;
   const int ntw = kw_end > kbeg ? (kw_end - kbeg + 31) / 32 : 0;
   if constexpr (SPLIT) {
-    raw.store(smA, tid);
+    raw.store(smA, tid, a.big);
     if (nstage > 1) load_raw(kbeg + KS);
   } else {
     issue_stage(kbeg, smA);
@@ -690,7 +704,7 @@ __global__ __launch_bounds__(kThreads, kWavesPerSimd) void rowstats_kernel(P1Arg
     wait_vmem();
     __syncthreads();  // stage st is in LDS; every wave is done with the other buffer
     if constexpr (SPLIT) {
-      if (st + 1 < nstage) raw.store(nxt, tid);
+      if (st + 1 < nstage) raw.store(nxt, tid, a.big);
       if (st + 2 < nstage) load_raw(ks + 2 * KS);
     } else {
       if (st + 1 < nstage) issue_stage(ks + KS, nxt);
@@ -893,7 +907,7 @@ struct P2Args {
   const int32_t *cu_seqlens, *cu_text, *text_pos;
   int B, Hq, Hkv, G, T_tot, N_tok, nkb, nqs;
   int nsl, ppx, kps;  // key-block slices per unit, (unit, slice) pairs per XCD, blocks per pair
-  float cl2e;
+  float cl2e, big;
   float *colsum;  // [nqs][Hkv][N_tok]
 };
 
@@ -969,7 +983,7 @@ __global__ __launch_bounds__(kThreads, kWavesPerSimd) void colsum_kernel(P2Args 
     if (key < L) {
       const char *src = a.k + ((size_t)(s0 + key) * a.Hkv + g) * ROWB + hi * E * sizeof(T);
 #pragma unroll
-      for (int s = 0; s < NS; ++s) kf[j][s] = mem_frag<T>(src + s * 2 * E * sizeof(T));
+      for (int s = 0; s < NS; ++s) kf[j][s] = mem_frag<T>(src + s * 2 * E * sizeof(T), a.big);
     } else {
 #pragma unroll
       for (int s = 0; s < NS; ++s) kf[j][s] = frag{};
@@ -1009,7 +1023,7 @@ __global__ __launch_bounds__(kThreads, kWavesPerSimd) void colsum_kernel(P2Args 
   };
   auto issue_stage = [&](int rs, QTile &dst) __attribute__((always_inline)) {
     if constexpr (SPLIT) {
-      raw.store(dst.q, tid);  // (loaded a stage ago)
+      raw.store(dst.q, tid, a.big);  // (loaded a stage ago)
     } else if (g_pow2 && rs + QR <= R) {
       int ln = lane;
       asm volatile("" : "+v"(ln));
@@ -1285,6 +1299,7 @@ hipError_t run_row_lse(hipStream_t st, const DevLayout &L, const AttnPlan &P, co
   a.nkc = P.nkc;
   a.kchunk = P.kchunk;
   a.cl2e = scale * kLog2e;
+  a.big = split_big(D, a.cl2e);
   a.part_m = (float *)(ws + P.off_part_m);
   a.part_l = (float *)(ws + P.off_part_l);
   const int nunits = L.B * Hkv * P.nkc;
@@ -1329,6 +1344,7 @@ hipError_t run_colsum(hipStream_t st, const DevLayout &L, const AttnPlan &P, con
   a.nkb = P.nkb;
   a.nqs = P.nqs;
   a.cl2e = scale * kLog2e;
+  a.big = split_big(D, a.cl2e);
   a.colsum = (float *)(ws + P.off_colsum);
   a.nsl = P.nsl;
   a.ppx = (L.B * Hkv * P.nsl + 7) / 8;

@@ -67,6 +67,69 @@ def test_an_infinite_key_value_with_negative_logits(d):
     np.testing.assert_allclose(s[vis], s_o[vis], rtol=TOL["fp32"])
 
 
+def _check(lay, q, k, Hq, Hkv, d):
+    dl = A.DeviceLayout(lay)
+    s, isum = A.score_attn(dl, torch.from_numpy(q).cuda(), torch.from_numpy(k).cuda(), d ** -0.5)
+    s_o, isum_o, _, _ = O.attn_scores(lay, q, k, Hq, Hkv, d ** -0.5, "fp32")
+    vis = lay.visual_mask()
+    np.testing.assert_allclose(s.cpu().numpy()[vis], s_o[vis], rtol=TOL["fp32"])
+    np.testing.assert_allclose(isum.cpu().numpy(), isum_o, rtol=TOL["fp32"])
+
+
+@pytest.mark.parametrize("small", ["q", "k"])
+@pytest.mark.parametrize("case", [CASES[3], CASES[5], CASES[7]], ids=lambda c: f"d{c[0]}h{c[1]}-{c[2]}")
+def test_operands_at_both_ends_of_the_range(case, small):
+    """Operands near 2^-122 against operands near 2^122: the third bf16 part of
+    the small ones is below bf16's smallest step, their products are ordinary."""
+    need_gpu()
+    say(f"fp32 scores, {small} near 2^-122, {case}")
+    lay, q, k = _draw(case, 13)
+    lo, hi = np.float32(2.0 ** -122), np.float32(2.0 ** 122)
+    q, k = (q * lo, k * hi) if small == "q" else (q * hi, k * lo)
+    assert np.isfinite(q).all() and np.isfinite(k).all()
+    d, Hq, Hkv = case[:3]
+    _check(lay, q, k, Hq, Hkv, d)
+
+
+@pytest.mark.parametrize("d", [64, 128])
+def test_finite_values_that_round_to_infinity_in_bf16(d):
+    need_gpu()
+    say(f"fp32 scores, finite overflow of bf16, d={d}")
+    lay, q, k = _draw((d, 4, 2, [[200, 100], [33]], 2, 20), 5)
+    top = np.float32(3.4e38)                       # bf16 ends at 3.39e38
+    assert torch.isinf(torch.tensor(top).bfloat16())
+    q[:, :, 3] *= np.float32(1e-38)
+    k[int(lay.img_start[0]) + 40, :, 3] = top
+    k[int(lay.img_start[2]) + 32, :, 3] = -top
+    _check(lay, q, k, 4, 2, d)
+
+
+@pytest.mark.parametrize("value", [np.nan, np.inf, -np.inf], ids=str)
+@pytest.mark.parametrize("d", [64, 128])
+def test_a_query_that_is_not_finite(d, value):
+    """One text row before the second image whose logits are not numbers (or all
+    infinite): the tokens it sees score NaN and are flagged, the others are as
+    the oracle has them."""
+    need_gpu()
+    say(f"fp32 scores, a query of {value}, d={d}")
+    lay, q, k = _draw((d, 4, 2, [[90, 150], [70]], 2, 20), 6)
+    k[:, :, 3] = np.abs(k[:, :, 3]) + 0.1
+    q_bad = q.copy()
+    q_bad[3, 1, 3] = value                         # the second of the rows between the images
+    dl = A.DeviceLayout(lay)
+    status = torch.zeros(lay.B, dtype=torch.int32, device="cuda")
+    s, _ = A.score_attn(dl, torch.from_numpy(q_bad).cuda(), torch.from_numpy(k).cuda(), d ** -0.5,
+                        status=status)
+    s_o, _, _, _ = O.attn_scores(lay, q, k, 4, 2, d ** -0.5, "fp32")
+    s, vis = s.cpu().numpy(), lay.visual_mask()
+    a, n = int(lay.img_start[0]), int(lay.img_len[0])
+    assert int(lay.text_pos[3]) > a + n > int(lay.text_pos[1])
+    assert np.isnan(s[a:a + n]).all()
+    assert [x & 1 for x in status.tolist()] == [1, 0]
+    vis[a:a + n] = False
+    np.testing.assert_allclose(s[vis], s_o[vis], rtol=TOL["fp32"])
+
+
 @pytest.mark.parametrize("d", [64, 128])
 def test_partly_filled_row_tiles_cost_no_more_than_full_ones(d):
     """40 query rows per key head (a full row tile and one of 8 rows) against 64
