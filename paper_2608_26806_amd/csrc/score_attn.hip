@@ -148,6 +148,13 @@ __host__ __device__ constexpr int tiles_pass2(int d, int planes) {
   return 96 / (planes * d / 4) < 1 ? 1 : (96 / (planes * d / 4) > 4 ? 4 : 96 / (planes * d / 4));
 }
 
+// Rows per LDS stage, both passes.  bf16: 128 rows, by direct-to-LDS loads.
+// fp32: the rows are loaded to registers, split and stored, 24 KB of planes
+// per stage, so that two blocks fit on a CU with two stages each.
+__host__ __device__ constexpr int stage_rows(int d, int planes) {
+  return planes > 1 ? 24576 / (planes * d * 2) : kStage;
+}
+
 template <typename T, int D>
 struct Geo {
   static constexpr bool SPLIT = Mma<T>::NP > 1;
@@ -158,10 +165,7 @@ struct Geo {
   static constexpr int NT2 = tiles_pass2(D, Mma<T>::NP);   // key tiles per wave, pass 2
   static constexpr int NCH = PROWB / 16;               // 16-byte chunks per LDS row
   static constexpr int SWZ = (NCH < 16 ? NCH : 16) - 1;  // XOR swizzle of the chunk index
-  // Rows per stage, both passes.  bf16: 128 rows, by direct-to-LDS loads.
-  // fp32: the rows are loaded to registers, split and stored, 24 KB of planes
-  // per stage, so that two blocks fit on a CU with two stages each.
-  static constexpr int STAGE = SPLIT ? 24576 / (3 * PROWB) : kStage;
+  static constexpr int STAGE = stage_rows(D, Mma<T>::NP);
   static constexpr int SBYTES = STAGE * PROWB * Mma<T>::NP;
 };
 
@@ -1471,7 +1475,14 @@ AttnPlan attn_plan(const DevLayout &L, int Hq, int Hkv, int d, int dtype) {
     const long long min_rows = base2 < 256 ? kStage : 512;
     const long long cap = (P.rows_max + min_rows - 1) / min_rows;
     if (nq > cap) nq = cap;
-    P.nqs = nq < 1 ? 1 : (int)nq;
+    if (nq < 1) nq = 1;
+    // A split is whole stages (colsum_kernel rounds its rows up), so the last
+    // ones may be left without rows: they would load their keys, write planes
+    // of zeros and have them read again.  Three sequences of six images, 497
+    // rows, d = 64: three splits of which two hold rows.
+    const long long st = stage_rows(d, fp32 ? 3 : 1);
+    const long long per = ((P.rows_max + nq - 1) / nq + st - 1) / st * st;
+    P.nqs = per > 0 ? (int)((P.rows_max + per - 1) / per) : 1;
   }
   const size_t rows = (size_t)Hq * L.T_tot;
   size_t off = 0;

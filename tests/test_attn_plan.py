@@ -1,0 +1,53 @@
+"""The launch plan of the attention score, on the CPU: a host program linked
+against libavtp.so prints it for a range of layouts."""
+import os
+import shutil
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+LIBDIR = os.path.join(ROOT, "paper_2608_26806_amd")
+
+PROGRAM = r"""
+#include <cstdio>
+#include "avtp_internal.h"
+int main() {
+  const int heads[][2] = {{4, 2}, {14, 2}, {16, 16}, {28, 4}, {32, 8}, {256, 1}};
+  const int text[] = {0, 1, 7, 20, 37, 64, 71, 129, 200, 512, 1000}, batch[] = {1, 3, 8, 30};
+  const int len[] = {33, 311, 1976, 4157, 16584};
+  for (int B : batch) for (int L : len) for (int T : text) for (auto &h : heads)
+    for (int d : {64, 128}) for (int dt : {AVTP_BF16, AVTP_FP32}) {
+      if (T > L) continue;
+      avtp::DevLayout lay{};
+      lay.B = B; lay.N_tok = B * L; lay.T_tot = B * T; lay.max_seqlen = L; lay.max_text = T;
+      const avtp::AttnPlan p = avtp::attn_plan(lay, h[0], h[1], d, dt);
+      std::printf("%d %d %d %d %d %d %d %d %d\n", B, L, h[0], h[1], d, dt, p.rows_max, p.nqs, p.nkt2);
+    }
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def plans(tmp_path_factory):
+    """(B, longest sequence, Hq, Hkv, d, dtype, most query rows, query splits, key tiles)"""
+    assert shutil.which("g++")
+    tmp = tmp_path_factory.mktemp("plan")
+    src, exe = tmp / "plan.cpp", tmp / "plan"
+    src.write_text(PROGRAM)
+    subprocess.run(["g++", "-std=c++17", "-w", "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include",
+                    "-I" + os.path.join(LIBDIR, "csrc"), str(src), "-L" + LIBDIR, "-lavtp",
+                    "-Wl,-rpath," + LIBDIR, "-Wl,-rpath,/opt/rocm/lib", "-L/opt/rocm/lib",
+                    "-lamdhip64", "-o", str(exe)], check=True)
+    out = subprocess.run([str(exe)], check=True, capture_output=True, text=True).stdout
+    return [tuple(map(int, line.split())) for line in out.splitlines()]
+
+
+def test_every_query_split_of_the_longest_sequence_holds_rows(plans):
+    """Splits are whole stages: 128 rows in bf16, 24 KB of three bf16 planes in fp32."""
+    assert len(plans) > 2000
+    for p in plans:
+        d, dtype, rows, nqs = p[4:8]
+        stage = 128 if dtype == 0 else 24576 // (6 * d)
+        per = -(-(-(-rows // nqs)) // stage) * stage
+        assert nqs == 1 or (nqs - 1) * per < rows, p
