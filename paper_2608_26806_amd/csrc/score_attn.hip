@@ -1441,17 +1441,24 @@ AttnPlan attn_plan(const DevLayout &L, int Hq, int Hkv, int d, int dtype) {
   // 96 text rows (336 -> 512 blocks): pass 2 34.5 -> 29.2 us; one sequence of
   // 4 x 729 tokens: 15.3 -> 12.8 (two tiles) -> 12.3 us (one).  At 2,432
   // blocks three tiles stay faster (8 x 16 images: 108-113 against 119-124).
-  // d = 64: 3 sequences of 6 images, 14 heads, 24 -> 180 blocks, 14.1 -> 11.3 us.
   auto key_blocks = [&](int nt) { return (L.max_seqlen + 4 * nt * 32 - 1) / (4 * nt * 32); };
+  auto blocks2 = [&](int nt) { return (long long)L.B * Hkv * key_blocks(nt); };
+  // bf16 at d = 64 has half the work per tile and room for more blocks per CU:
+  // below 512 blocks of four tiles, two tiles only where they give 512 blocks of
+  // more than one stage, else one, and the rows are split further (below).
+  // Score with a given LSE, four tiles and their splits -> two and one by the
+  // rule above -> this: 8 x 8 images of 512 tokens, 14/2 heads, 19.3 -> 21.9 ->
+  // 18.5 us; 30 x 3 of 100, 16/16 heads, 13.8 -> 14.9 -> 13.3; 2 x 16 of 512,
+  // 28/4 heads, 42.3 -> 46.9 -> 39.0; 3 x 6 of 300, 14/2 heads, 14.8 -> 11.1 ->
+  // 11.1.
+  const bool wide64 = nkt2 == 4;
+  if (wide64) {
+    if (blocks2(4) < 512) nkt2 = P.rows_max > kStage && blocks2(2) >= 512 ? 2 : 1;
+  } else {
+    if (nkt2 > 2 && blocks2(nkt2) < 512) nkt2 = 2;
+    if (nkt2 > 1 && blocks2(nkt2) < 256) nkt2 = 1;
+  }
   P.nkb = key_blocks(nkt2);
-  if (nkt2 > 2 && (long long)L.B * Hkv * P.nkb < 512) {
-    nkt2 = 2;
-    P.nkb = key_blocks(nkt2);
-  }
-  if (nkt2 > 1 && (long long)L.B * Hkv * P.nkb < 256) {
-    nkt2 = 1;
-    P.nkb = key_blocks(nkt2);
-  }
   if (P.nkb < 1) P.nkb = 1;
   P.nkt2 = nkt2;
   {  // slices per unit: the fewest that make the (unit, slice) pairs a multiple of 8
@@ -1475,6 +1482,17 @@ AttnPlan attn_plan(const DevLayout &L, int Hq, int Hkv, int d, int dtype) {
     const long long min_rows = base2 < 256 ? kStage : 512;
     const long long cap = (P.rows_max + min_rows - 1) / min_rows;
     if (nq > cap) nq = cap;
+    // The narrower blocks at d = 64: for 768 blocks (1,024: 4 x 4 images of 729
+    // tokens, 32/8 heads, 14.5 -> 16.4 us), and long rows every 512 up to 2,048
+    // blocks (3 x 16 of 1,024, 512 text rows, 14/2 heads: 111 -> 92 us), whose
+    // column sums take no more room than those of 512 blocks of four tiles.
+    if (wide64 && nkt2 < 4 && base2 >= 256) {
+      const long long stages = (P.rows_max + kStage - 1) / kStage;
+      const long long by_rows = P.rows_max / 512, most = (2048 + base2 - 1) / base2;
+      nq = (768 + base2 - 1) / base2;
+      if (nq < by_rows) nq = by_rows < most ? by_rows : most;
+      nq = stages > nq ? (stages + stages / nq - 1) / (stages / nq) : stages;
+    }
     if (nq < 1) nq = 1;
     // A split is whole stages (colsum_kernel rounds its rows up), so the last
     // ones may be left without rows: they would load their keys, write planes

@@ -22,7 +22,7 @@ int main() {
       avtp::DevLayout lay{};
       lay.B = B; lay.N_tok = B * L; lay.T_tot = B * T; lay.max_seqlen = L; lay.max_text = T;
       const avtp::AttnPlan p = avtp::attn_plan(lay, h[0], h[1], d, dt);
-      std::printf("%d %d %d %d %d %d %d %d %d\n", B, L, h[0], h[1], d, dt, p.rows_max, p.nqs, p.nkt2);
+      std::printf("%d %d %d %d %d %d %d %d %d %d\n", B, L, h[0], h[1], d, dt, p.rows_max, p.nqs, p.nkt2, p.nkb);
     }
 }
 """
@@ -30,7 +30,8 @@ int main() {
 
 @pytest.fixture(scope="module")
 def plans(tmp_path_factory):
-    """(B, longest sequence, Hq, Hkv, d, dtype, most query rows, query splits, key tiles)"""
+    """(B, longest sequence, Hq, Hkv, d, dtype, most query rows, query splits, key tiles,
+    key blocks)"""
     assert shutil.which("g++")
     tmp = tmp_path_factory.mktemp("plan")
     src, exe = tmp / "plan.cpp", tmp / "plan"
@@ -51,3 +52,16 @@ def test_every_query_split_of_the_longest_sequence_holds_rows(plans):
         stage = 128 if dtype == 0 else 24576 // (6 * d)
         per = -(-(-(-rows // nqs)) // stage) * stage
         assert nqs == 1 or (nqs - 1) * per < rows, p
+
+
+def test_narrow_blocks_at_head_size_64_fill_the_chip_as_the_wide_ones_did(plans):
+    """Where blocks of four key tiles give way to narrower ones there are 512
+    blocks, two per CU, or every stage of rows has a block of its own (fewer than
+    256 before the rows are split: within the rounding of a split to stages)."""
+    seen = 0
+    for B, L, Hq, Hkv, d, dtype, rows, nqs, nkt2, nkb in plans:
+        if d == 64 and dtype == 0 and nkt2 < 4 and rows:
+            seen += 1
+            blocks, want = B * Hkv * nkb, 512 if B * Hkv * nkb >= 256 else 256
+            assert blocks * nqs >= want or nqs == -(-rows // 128), (B, L, Hq, Hkv, rows, nqs, nkt2)
+    assert seen > 200
