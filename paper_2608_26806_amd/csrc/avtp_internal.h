@@ -46,6 +46,13 @@ struct AttnPlan {
 
 AttnPlan attn_plan(const DevLayout &L, int Hq, int Hkv, int d, int dtype);
 
+// r / G = umulhi(r, group_mul(G)) >> 1 for every G <= 256 that is no power of
+// two and every row r of a key head's group: with m = ceil(2^33 / G) the product
+// r m exceeds 2^33 r / G by less than r G / G, which stays below the next
+// multiple of 2^33 while r < 2^25 (the queries of a sequence are below 4 GiB, a
+// row of one head is 128 bytes or more).
+inline uint32_t group_mul(int G) { return (uint32_t)(((1ull << 33) + G - 1) / G); }
+
 // avtp_score with its workspace argument.  With ws_need set, only validates
 // the arguments (returning their error, if any) and stores the workspace the
 // call needs; nothing is launched and ws is not read.

@@ -910,6 +910,7 @@ struct P2Args {
   const float *lse2;  // row LSE in log2 units, [T_tot][Hq]
   const int32_t *cu_seqlens, *cu_text, *text_pos;
   int B, Hq, Hkv, G, T_tot, N_tok, nkb, nqs;
+  uint32_t g_mul;     // group_mul(G)
   int nsl, ppx, kps;  // key-block slices per unit, (unit, slice) pairs per XCD, blocks per pair
   float cl2e, big;
   float *colsum;  // [nqs][Hkv][N_tok]
@@ -1014,11 +1015,15 @@ __global__ __launch_bounds__(kThreads, kWavesPerSimd) void colsum_kernel(P2Args 
   // stage load has per-lane offsets fixed across stages.
   const int lg = __builtin_ctz((unsigned)a.G);
   const bool g_pow2 = (a.G & (a.G - 1)) == 0;
+  // The token of row r: r / G by the reciprocal that the host gave (group_mul).
+  auto row_tok = [&](int r) __attribute__((always_inline)) {
+    return g_pow2 ? r >> lg : (int)(__umulhi((uint32_t)r, a.g_mul) >> 1);
+  };
   // One stage: query rows [rs, rs + QR), their LSE and positions.  Wave 0
   // loads the LSE, wave 1 the positions, 64 rows per instruction.
   auto row_off = [&](int r) __attribute__((always_inline)) {
     r = min(r, R - 1);  // rows past R re-read row R-1 (their LSE is +inf)
-    const int t = g_pow2 ? r >> lg : r / a.G;
+    const int t = row_tok(r);
     return (uint32_t)(t * a.Hq + (r - t * a.G)) * ROWB;
   };
   SplitStage<D> raw;  // fp32: rows on their way to LDS
@@ -1042,7 +1047,7 @@ __global__ __launch_bounds__(kThreads, kWavesPerSimd) void colsum_kernel(P2Args 
 #pragma unroll
       for (int i = 0; i < (QR + 63) / 64; ++i) {
         const int r = min(rs + i * 64 + lane, r_hi - 1);
-        const int t = g_pow2 ? r >> lg : r / a.G;
+        const int t = row_tok(r);
         if (wave == 0) load_lds4(lbase, dst.lse + i * 64, (uint32_t)(t * a.Hq + (r - t * a.G)) * 4u);
         else load_lds4(pbase, dst.pos + i * 64, (uint32_t)t * 4u);
       }
@@ -1347,6 +1352,7 @@ hipError_t run_colsum(hipStream_t st, const DevLayout &L, const AttnPlan &P, con
   a.N_tok = L.N_tok;
   a.nkb = P.nkb;
   a.nqs = P.nqs;
+  a.g_mul = group_mul(P.G);
   a.cl2e = scale * kLog2e;
   a.big = split_big(D, a.cl2e);
   a.colsum = (float *)(ws + P.off_colsum);
