@@ -368,10 +368,11 @@ int avtp_select_compact(avtp_stream_t stream, const avtp_layout *layout, const f
   // bytes to move).  Every block of the fused kernel runs its image's
   // selection before it copies, so the copies cannot start before the
   // selections end; with more bytes to move the two kernels back to back are
-  // as fast or faster (measured with events around the calls: 0.4 MB moved
-  // (128 visual tokens): one launch 12.2 us, two 12.8; 15 MB (4 images of
-  // 729 tokens): 17.0 and 16.2; 240 MB (2 sequences of 8 images): 39 and
-  // 34), and are used instead.
+  // as fast or faster (hidden states, positions, K and V, budget included:
+  // 0.2 MiB moved (2 x 64 visual tokens): one launch 9.0 us, two 10.7; 1.3 MiB
+  // (4 x 256): 9.8 and 11.0; 4.3 MiB (4 x 256): 12.1 and 11.1; 14 MiB (4 images
+  // of 729 tokens): 14.6 and 13.0; 51 MiB (2 sequences of 8 images of 512): 30
+  // and 19), and are used instead.
   const int64_t moved = bytes_moved(need, tensors, n_tensors);
   hipStream_t st = (hipStream_t)stream;
   if (moved > kFusedMaxBytes) {

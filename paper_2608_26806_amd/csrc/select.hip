@@ -403,8 +403,8 @@ __global__ __launch_bounds__(kThreads) void select_kernel(SelArgs A, RuleArgs R,
 // Fused selection and compaction: S blocks per image (slices).  Every slice
 // runs the image's selection (its keys are few and sit in LDS), owns the
 // output rows o with o mod S == slice, writes their keep_idx entries, lists
-// them in LDS, and then copies those rows of every tensor as one run of
-// vector units.  No block waits for another.
+// them in LDS, and then copies those rows of every tensor, as one run of vector
+// units or one tensor after the other (copy_flat).  No block waits for another.
 constexpr int kListCap = 4096;  // output rows one slice may own (the host sizes S for it)
 
 struct SCArgs {
@@ -453,12 +453,10 @@ struct UnitJob {
   }
 };
 
-// The listed rows of every tensor, as one run of vector units: a block has few
-// rows (4 MiB over about 1024 blocks), so what counts is that all its loads are
-// in flight at once, two per thread at a time.  One tensor after the other, a
-// round of memory latency each, the call took 10.6 us at 2 x 64 tokens with
-// hidden states, positions, K and V; as one run 9.1.
-__device__ inline void copy_listed(const CTensor *t, const uint32_t *unit_begin, int n_t,
+// The listed rows of every tensor, as one run of vector units, two per thread at
+// a time: for few units per block (copy_flat), where what counts is that the
+// tensors' loads are in flight together.
+__device__ inline void copy_units(const CTensor *t, const uint32_t *unit_begin, int n_t,
                                    uint32_t row_units, const int *lo, const int *lj, int n) {
   const uint32_t total = (uint32_t)n * row_units;
   auto job = [&](uint32_t x) __attribute__((always_inline)) {
@@ -487,13 +485,28 @@ __device__ inline void copy_listed(const CTensor *t, const uint32_t *unit_begin,
   }
 }
 
-template <int MODE>
+// The listed rows of one tensor, a power-of-two group of lanes per row (as in
+// the compaction kernel), four rows per group at once.
+template <typename V>
+__device__ inline void copy_rows(const CTensor &T, const int *lo, const int *lj, int n) {
+  const int lane = threadIdx.x & ((1 << T.lpr_shift) - 1);
+  const int per_pass = kThreads >> T.lpr_shift;
+  for (int p = 0; p < T.planes; ++p)
+    copy_rows_batched<V, false>(T, p, (long long)(threadIdx.x >> T.lpr_shift), n, per_pass, lane,
+                         [&](long long e, long long &j, long long &r) __attribute__((always_inline)) {
+                           j = lj[e];
+                           r = lo[e];
+                           return true;
+                         });
+}
+
+template <int MODE, bool FLAT>
 __global__ __launch_bounds__(kThreads) void select_compact_kernel(SCArgs a, RuleArgs R) {
   __shared__ int list_o[kListCap], list_j[kListCap];
   __shared__ int list_n;
-  __shared__ CTensor tensors[AVTP_MAX_TENSORS];  // (indexed per thread by the copy)
-  __shared__ uint32_t unit_begin[AVTP_MAX_TENSORS];
-  if ((int)threadIdx.x < a.n_t) {
+  __shared__ CTensor tensors[FLAT ? AVTP_MAX_TENSORS : 1];  // (indexed per thread by the copy)
+  __shared__ uint32_t unit_begin[FLAT ? AVTP_MAX_TENSORS : 1];
+  if (FLAT && (int)threadIdx.x < a.n_t) {
     tensors[threadIdx.x] = a.t[threadIdx.x];
     unit_begin[threadIdx.x] = a.unit_begin[threadIdx.x];
   }
@@ -521,7 +534,49 @@ __global__ __launch_bounds__(kThreads) void select_compact_kernel(SCArgs a, Rule
   };
   select_image<MODE>(A, R, img, sl == 0, a.status, put);
   __syncthreads();
-  copy_listed(tensors, unit_begin, a.n_t, a.row_units, list_o, list_j, min(list_n, kListCap));
+  const int n = min(list_n, kListCap);
+  if constexpr (FLAT) {
+    copy_units(tensors, unit_begin, a.n_t, a.row_units, list_o, list_j, n);
+  } else {
+    for (int ti = 0; ti < a.n_t; ++ti) {
+      const CTensor &T = a.t[ti];
+      switch (T.vshift) {
+        case 4: copy_rows<uint4>(T, list_o, list_j, n); break;
+        case 3: copy_rows<uint2>(T, list_o, list_j, n); break;
+        case 2: copy_rows<uint32_t>(T, list_o, list_j, n); break;
+        case 1: copy_rows<uint16_t>(T, list_o, list_j, n); break;
+        default: copy_rows<uint8_t>(T, list_o, list_j, n); break;
+      }
+    }
+  }
+}
+
+// Whether a block copies its rows as one run of vector units: with at most four
+// units per five threads for every plane of every tensor.  The run saves a round
+// of memory latency per plane and pays about 1 us per two units and thread (the
+// unit's row, tensor and plane are found with two divisions and a search),
+// against 0.2 us row by row.  2 x 64 tokens with hidden states, positions, K and
+// V: the call 10.6 -> 9.1 us as one run.  Row by row and as one run over 4 MiB
+// and less, one to eight images: 0.3-0.77 units per thread and plane, four
+// tensors 10.4-28.6 -> 9.5-28.2 us (up to 13 % less), one tensor the same; 0.88
+// 14.8 -> 16.1, 1.4 11.0 -> 11.9; one image of 64 tokens in rows of 42,816 bytes
+// (10.5) 9.8 -> 13.5, of 42,815 bytes (167 one-byte units) 24 -> 99.
+static bool copy_flat(const DevLayout &L, const SCArgs &a) {
+  const long long blocks = (long long)(L.n_img > 0 ? L.n_img : 1) * a.S;
+  const long long rows = (a.n_out + blocks - 1) / blocks;
+  long long planes = 0;
+  for (int i = 0; i < a.n_t; ++i) planes += a.t[i].planes;
+  return 5 * rows * a.row_units <= 4 * kThreads * planes;
+}
+
+// Launches the kernel of mode MODE in the form that copy_flat says.
+template <int MODE>
+static void launch_fused(hipStream_t st, const DevLayout &L, const SCArgs &a, const RuleArgs &R) {
+  const dim3 grid((unsigned)((L.n_img > 0 ? L.n_img : 1) * a.S));
+  if (copy_flat(L, a))
+    hipLaunchKernelGGL((select_compact_kernel<MODE, true>), grid, dim3(kThreads), 0, st, a, R);
+  else
+    hipLaunchKernelGGL((select_compact_kernel<MODE, false>), grid, dim3(kThreads), 0, st, a, R);
 }
 
 // Blocks per image of the one-launch selection + compaction: about 1024
@@ -574,9 +629,7 @@ hipError_t launch_select_compact(hipStream_t st, const DevLayout &L, const float
   clear_pending_error();
   const SCArgs a = sc_args(L, scores, budget, keep_idx, keep_capacity, cu_out, status, n_out,
                            tensors, n_tensors);
-  const int images = L.n_img > 0 ? L.n_img : 1;
-  hipLaunchKernelGGL(select_compact_kernel<kBudGlobal>, dim3((unsigned)(images * a.S)), dim3(kThreads),
-                     0, st, a, RuleArgs{});
+  launch_fused<kBudGlobal>(st, L, a, RuleArgs{});
   return hipGetLastError();
 }
 
@@ -620,14 +673,12 @@ hipError_t launch_budget_select_compact(hipStream_t st, const DevLayout &L, cons
   clear_pending_error();
   const SCArgs a = sc_args(L, scores, budget, keep_idx, keep_capacity, cu_out, status, n_out,
                            tensors, n_tensors);
-  const int images = L.n_img > 0 ? L.n_img : 1;
   const RuleArgs R =
       rule_args(L, img_sum, mode, alpha, lo_permille, hi_permille, floor_abs, budget);
-  const dim3 grid((unsigned)(images * a.S));
   if (L.max_img_per_seq <= kWaveBudgetMaxImages)
-    hipLaunchKernelGGL(select_compact_kernel<kBudWave>, grid, dim3(kThreads), 0, st, a, R);
+    launch_fused<kBudWave>(st, L, a, R);
   else
-    hipLaunchKernelGGL(select_compact_kernel<kBudBlock>, grid, dim3(kThreads), 0, st, a, R);
+    launch_fused<kBudBlock>(st, L, a, R);
   return hipGetLastError();
 }
 

@@ -43,3 +43,54 @@ def test_rows_of_every_unit_width_and_planes(imgs):
     assert n == lay.T_tot + int(budget.sum()) and np.all(np.diff(idx.cpu().numpy()) > 0)
     for s, d, td in pairs:
         assert torch.equal(d.narrow(td, 0, n), s.index_select(td, idx)), (s.dtype, tuple(s.shape))
+
+
+@pytest.mark.parametrize("n, row_bytes", [(64, 42816), (64, 42815), (729, 5393)])
+def test_one_launch_is_not_slower_than_two_below_its_limit(n, row_bytes):
+    """Rows of many vector units just below the 4 MiB that the one launch serves:
+    it must not take longer than the selection and the compaction one after the
+    other (row by row it takes less; with every unit looked up on its own it
+    took up to six times as long)."""
+    need_gpu()
+    say(f"one launch against two, {n} tokens, rows of {row_bytes} bytes")
+    lay = build_layout([[n]], 0, 16, 50)
+    dl = A.DeviceLayout(lay)
+    src = torch.randint(0, 256, (dl.N_tok, row_bytes), device="cuda").to(torch.uint8)
+    dst = torch.zeros(dl.N_out, row_bytes, dtype=torch.uint8, device="cuda")
+    assert 2 * dl.N_out * row_bytes <= 4 << 20
+    scores = torch.rand(dl.N_tok, device="cuda")
+    budget = torch.tensor(lay.keep_total, dtype=torch.int32, device="cuda")
+    keep = torch.empty(dl.N_out, dtype=torch.int32, device="cuda")
+    cu = torch.empty(2, dtype=torch.int32, device="cuda")
+    ts = A.TensorSet([(src, dst, 0)])
+
+    def one():
+        A.select_compact(dl, scores, budget, ts, keep_idx=keep, cu_out=cu)
+
+    def two():
+        A.select(dl, scores, budget, keep_idx=keep, cu_out=cu)
+        A.compact(dl, keep, ts)
+
+    graphs = []
+    for call in (one, two):
+        call()
+        torch.cuda.synchronize()
+        g = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(g):
+            for _ in range(20):
+                call()
+        graphs.append(g)
+
+    def us(g):
+        a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        a.record()
+        g.replay()
+        b.record()
+        b.synchronize()
+        return a.elapsed_time(b) * 50
+
+    t = [min(us(g) for _ in range(9)) for g in graphs]
+    say(f"one launch {t[0]:.1f} us, two {t[1]:.1f} us")
+    assert torch.equal(dst, src[keep.long()])
+    # (the best of nine runs of 20 calls varies by a few per cent)
+    assert t[0] < 1.25 * t[1]
