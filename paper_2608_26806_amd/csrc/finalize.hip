@@ -42,15 +42,7 @@ __global__ __launch_bounds__(kThreads) void finalize_kernel(
   }
   const int i = blockIdx.x;
   const int s0 = img_start[i], n = img_len[i];
-  int b = 0;  // the sequence holding image i
-  for (int c0 = 0; c0 < B; c0 += 64) {
-    const int c = c0 + lane;
-    const unsigned long long m = __ballot(c < B && cu_img[c] <= i && i < cu_img[c + 1]);
-    if (m) {
-      b = c0 + __builtin_ctzll(m);
-      break;
-    }
-  }
+  const int b = wave::segment_of(cu_img, B, i).b;  // the sequence holding image i
   // the column sums of token j over the planes, in plane order
   auto plane_sum = [&](int j) __attribute__((always_inline)) {
     const float *p = colsum + s0 + j;

@@ -216,19 +216,8 @@ __device__ __attribute__((always_inline)) inline void select_image(const SelArgs
   // is bound by that chain (the one-launch form at 2 x 64 tokens 9.05 -> 8.82
   // us, the selection alone at 32 images of 1,024 tokens 16.6 -> 16.3).
   const int st = img_start[i], n = img_len[i];
-  int b = 0, i0 = 0, i1 = 0;
-  for (int c0 = 0; c0 < B; c0 += 64) {
-    const int c = min(c0 + (tid & 63), B - 1);
-    const int lo = cu_img[c], hi = cu_img[c + 1];
-    const unsigned long long m = __ballot(lo <= i && i < hi);
-    if (m) {
-      const int src = __builtin_ctzll(m);
-      b = c0 + src;
-      i0 = __builtin_amdgcn_readlane(lo, src);
-      i1 = __builtin_amdgcn_readlane(hi, src);
-      break;
-    }
-  }
+  const wave::Segment seq = wave::segment_of(cu_img, B, i);
+  const int b = seq.b, i0 = seq.lo, i1 = seq.hi;
   if (tid == 0) cnt[0] = cnt[1] = 0;
   __syncthreads();  // (the counts are cleared)
   const bool in_lds = n <= kLdsKeys;
