@@ -10,8 +10,6 @@
 namespace avtp {
 namespace {
 
-constexpr int kThreads = 1024;
-constexpr int kWaves = kThreads / 64;
 constexpr int kPlanesInFlight = 8;
 
 // Per-image epilogue shared by both score modes: s_j from the column sums
@@ -20,18 +18,21 @@ constexpr int kPlanesInFlight = 8;
 // the text positions.  One block per image.
 //
 // A few hundred blocks of dependent loads: bound by latency, so a token has a
-// thread of its own (1024 per block) with eight planes' loads in flight, every
+// thread of its own (kThreads = 1024) with eight planes' loads in flight, every
 // wave finds the image's sequence itself (no barrier before the loads), and the
 // text-row count runs while the planes arrive.  With 256 threads, four tokens
 // each and the rest of a longer image one plane after the other: two sequences
 // of 8 images of 256-1,536 tokens 8.7 -> 4.8 us, 8 x 16 images 8.1 -> 5.2, 4 x
-// 729 tokens 4.5 -> 3.9.
+// 729 tokens 4.5 -> 3.9.  Blocks of 256 threads serve short or many images, see
+// launch_finalize.
+template <int kThreads>
 __global__ __launch_bounds__(kThreads) void finalize_kernel(
     const float *__restrict__ colsum, int Hq, int planes, int N_tok, int n_img, int T_tot,
     const int32_t *__restrict__ img_start, const int32_t *__restrict__ img_len,
     const int32_t *__restrict__ cu_img, const int32_t *__restrict__ cu_text,
     const int32_t *__restrict__ text_pos, int B, float *__restrict__ scores,
     float *__restrict__ img_sum, int32_t *__restrict__ status) {
+  constexpr int kWaves = kThreads / 64;
   __shared__ float red[kWaves];
   __shared__ int cnt[kWaves];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -105,10 +106,21 @@ __global__ __launch_bounds__(kThreads) void finalize_kernel(
 hipError_t launch_finalize(hipStream_t st, const DevLayout &L, const float *colsum, int Hq,
                            int planes, float *scores, float *img_sum, int32_t *status) {
   clear_pending_error();
-  const int text_blocks = (L.T_tot + kThreads - 1) / kThreads;
+  // 1024 threads per image where most of them have a token and the blocks run at
+  // once, two on a CU.  Else 256: the waves without a token cost their start and
+  // the barriers, and with several rounds of blocks other images cover an
+  // image's latency.  Score with a given LSE and variation score, 1024 against
+  // 256 threads: 8,192 images of 49 tokens 76 and 106 -> 58 and 96 us, 512 of 64
+  // tokens 23.0 and 10.0 -> 22.7 and 9.8; 2,048 of 729 tokens 222 -> 218
+  // (variation); 512 of 1,024 tokens 271 -> 274 and 79.3 -> 79.8, 128 of 1,024
+  // 61.2 -> 62.9 and 23.6 -> 24.2.
+  const bool wide = L.max_img_len > 256 && L.n_img <= 512;
+  const int threads = wide ? 1024 : 256;
+  const int text_blocks = (L.T_tot + threads - 1) / threads;
   const int grid = L.n_img + text_blocks;
   if (grid == 0) return hipSuccess;
-  hipLaunchKernelGGL(finalize_kernel, dim3(grid), dim3(kThreads), 0, st, colsum, Hq, planes, L.N_tok,
+  const auto kernel = wide ? finalize_kernel<1024> : finalize_kernel<256>;
+  hipLaunchKernelGGL(kernel, dim3(grid), dim3(threads), 0, st, colsum, Hq, planes, L.N_tok,
                      L.n_img, L.T_tot, L.img_start, L.img_len, L.cu_img, L.cu_text, L.text_pos,
                      L.B, scores, img_sum, status);
   return hipGetLastError();
