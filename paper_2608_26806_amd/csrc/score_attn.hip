@@ -1450,8 +1450,9 @@ AttnPlan attn_plan(const DevLayout &L, int Hq, int Hkv, int d, int dtype) {
   auto key_blocks = [&](int nt) { return (L.max_seqlen + 4 * nt * 32 - 1) / (4 * nt * 32); };
   auto blocks2 = [&](int nt) { return (long long)L.B * Hkv * key_blocks(nt); };
   // bf16 at d = 64 has half the work per tile and room for more blocks per CU:
-  // below 512 blocks of four tiles, two tiles only where they give 512 blocks of
-  // more than one stage, else one, and the rows are split further (below).
+  // below 512 blocks of four tiles, two tiles only where they give 512 blocks,
+  // of more than one stage or with no fewer key tiles than one would take, else
+  // one, and the rows are split further (below).
   // Score with a given LSE, four tiles and their splits -> two and one by the
   // rule above -> this: 8 x 8 images of 512 tokens, 14/2 heads, 19.3 -> 21.9 ->
   // 18.5 us; 30 x 3 of 100, 16/16 heads, 13.8 -> 14.9 -> 13.3; 2 x 16 of 512,
@@ -1459,7 +1460,8 @@ AttnPlan attn_plan(const DevLayout &L, int Hq, int Hkv, int d, int dtype) {
   // 11.1.
   const bool wide64 = nkt2 == 4;
   if (wide64) {
-    if (blocks2(4) < 512) nkt2 = P.rows_max > kStage && blocks2(2) >= 512 ? 2 : 1;
+    const bool two = blocks2(2) >= 512 && (P.rows_max > kStage || blocks2(1) >= 2 * blocks2(2));
+    if (blocks2(4) < 512) nkt2 = two ? 2 : 1;
   } else {
     if (nkt2 > 2 && blocks2(nkt2) < 512) nkt2 = 2;
     if (nkt2 > 1 && blocks2(nkt2) < 256) nkt2 = 1;
@@ -1489,15 +1491,16 @@ AttnPlan attn_plan(const DevLayout &L, int Hq, int Hkv, int d, int dtype) {
     const long long cap = (P.rows_max + min_rows - 1) / min_rows;
     if (nq > cap) nq = cap;
     // The narrower blocks at d = 64: for 768 blocks (1,024: 4 x 4 images of 729
-    // tokens, 32/8 heads, 14.5 -> 16.4 us), and long rows every 512 up to 2,048
-    // blocks (3 x 16 of 1,024, 512 text rows, 14/2 heads: 111 -> 92 us), whose
-    // column sums take no more room than those of 512 blocks of four tiles.
+    // tokens, 32/8 heads, 14.5 -> 16.4 us) of at least two stages (of one: 2 x 9
+    // of 775, 286 rows, 12/12 heads, 23.2 -> 27.1 us), and long rows every 512 up
+    // to 2,048 blocks (3 x 16 of 1,024, 512 text rows, 14/2 heads: 111 -> 92 us),
+    // whose column sums take no more room than those of 512 blocks of four tiles.
     if (wide64 && nkt2 < 4 && base2 >= 256) {
       const long long stages = (P.rows_max + kStage - 1) / kStage;
       const long long by_rows = P.rows_max / 512, most = (2048 + base2 - 1) / base2;
       nq = (768 + base2 - 1) / base2;
+      if (nq > stages / 2) nq = stages / 2;
       if (nq < by_rows) nq = by_rows < most ? by_rows : most;
-      nq = stages > nq ? (stages + stages / nq - 1) / (stages / nq) : stages;
     }
     if (nq < 1) nq = 1;
     // A split is whole stages (colsum_kernel rounds its rows up), so the last
