@@ -11,23 +11,35 @@ from paper_2608_26806_amd.workloads import build_layout
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("imgs", [[[1]], [[49, 3]], [[65], [200, 31, 7]]], ids=str)
-def test_rows_of_every_unit_width_and_planes(imgs):
+# (images, width: rows `width` times as wide; the wide ones are copied row by row,
+# the others as one run of units, all of them in one launch)
+@pytest.mark.parametrize("imgs, width", [([[1]], 1), ([[49, 3]], 1), ([[65], [200, 31, 7]], 1),
+                                         ([[1]], 39), ([[49, 3]], 39), ([[65], [200, 31, 7]], 7)], ids=str)
+def test_rows_of_every_unit_width_and_planes(imgs, width):
     need_gpu()
-    say(f"fused copy units {imgs}")
+    say(f"fused copy units {imgs}, width {width}")
     lay = build_layout(imgs, 1, 5, 50)
     dl = A.DeviceLayout(lay)
     g = torch.Generator(device="cuda").manual_seed(7)
-    draw = lambda *s, dt=torch.uint8: torch.randint(0, 255, s, generator=g, device="cuda").to(dt)  # noqa: E731
-    N = dl.N_tok
-    srcs = [(draw(N, 1), 0), (draw(N, 3, dt=torch.int16), 0), (draw(3, N, 5, dt=torch.int32), 1),
-            (draw(3, N, dt=torch.int64), 1), (draw(N, 8, dt=torch.int16), 0), (draw(N, 2, 264, dt=torch.int16), 0),
-            (draw(2, N, 7), 1), (draw(N, 34, dt=torch.int32), 0)]
+
+    def draw(*s, dt=torch.uint8):
+        """Every byte of every element drawn on its own."""
+        es = dt.itemsize
+        return torch.randint(0, 256, (*s, es), generator=g, device="cuda").to(torch.uint8).view(dt).view(s)
+
+    N, w = dl.N_tok, width
+    srcs = [(draw(N, w), 0), (draw(N, 3 * w, dt=torch.int16), 0), (draw(3, N, 5 * w, dt=torch.int32), 1),
+            (draw(3, N, dt=torch.int64), 1), (draw(N, 8 * w, dt=torch.int16), 0),
+            (draw(N, 2, 264 * w, dt=torch.int16), 0), (draw(2, N, 7 * w), 1), (draw(N, 34 * w, dt=torch.int32), 0)]
+    row_bytes = sum(s.numel() * s.element_size() // N for s, _ in srcs)
+    assert 2 * dl.N_out * row_bytes <= 4 << 20
     pairs = []
     for s, td in srcs:
         shape = list(s.shape)
         shape[td] = dl.N_out
-        pairs.append((s, torch.full(shape, 99, dtype=s.dtype, device="cuda"), td))
+        # 0xA5 in every byte: a part of a unit that is not copied shows
+        fill = torch.full((*shape, s.element_size()), 0xA5, dtype=torch.uint8, device="cuda")
+        pairs.append((s, fill.view(s.dtype).view(shape), td))
     scores = torch.rand(N, generator=g, device="cuda")
     budget = torch.tensor([n // 2 for seq in imgs for n in seq], dtype=torch.int32, device="cuda")
     # keep totals of the layout are rounded per sequence: give the rest to the last image
