@@ -128,7 +128,10 @@ typedef struct {
  *   s_j = 1/Hq sum_h 1/|T_j| sum_{t in T_j} exp(c q_{t,h}.k_{j,g} - lse[h,t])
  * where T_j are the text rows after j.  Computed in two tiled passes over
  * the keys (row statistics, then column sums) with bf16 MFMA and fp32
- * accumulation; the attention matrix is never stored.  If row_lse is given
+ * accumulation; the attention matrix is never stored.  fp32 inputs run as three
+ * bf16 parts and six partial products (each product within 2^-24 of itself); over
+ * the whole range of fp32, for logits that meet very small, very large or
+ * infinite values the fp32 MFMA is used.  If row_lse is given
  * (e.g. the softmax LSE of the layer's own fused attention, natural log,
  * [Hq, T_tot] fp32) the first pass is skipped.
  *   q_text [T_tot, Hq, d]  queries of the text rows (dtype; may be NULL when

@@ -61,14 +61,19 @@ struct Mma<__bf16> {
   typedef bf16x8 frag;
   __device__ static inline f32x16 run(const frag &a, const frag &b, f32x16 c) { return mma(a, b, c); }
 };
-// fp32 inputs run on the bf16 MFMA too, 16 times the rate of the fp32 one: a
+// fp32 inputs run on the bf16 MFMA too, 16 times the rate of the fp32 one (the
+// three-part scheme of Henry, Tang and Heinecke, "Leveraging the bfloat16
+// Artificial Intelligence Datatype For Higher-Precision Computations", 2019): a
 // value is the sum of three bf16 numbers (8 bits each, remainders taken
 // exactly: nothing is lost above 2^-109, see split8) and a product is the six
-// partial products down to 2^-16 of it, smallest first; those left out are
-// below 2^-24 of it, the fp32 rounding.  A chain has 48 fp32 accumulations at
-// d = 128 where the fp32 MFMA has 64: the scores' error against 64 bits is the
-// same.  Two sequences of 8 images, 96 text rows, d = 128: both passes
-// 150 + 149 -> 77 + 65 us.
+// partial products down to 2^-16 of it, smallest first; the three left out are
+// below 2^-24 of it together, the fp32 rounding, and all of one sign where the
+// remainders of both sides are.  A chain has 48 fp32 accumulations at d = 128
+// where the fp32 MFMA has 64: the scores' error against 64 bits is no larger,
+// also with remainders of one sign (positive operands that end in 0x7fff, d =
+// 128: 3.1e-7 with the fp32 MFMA, 2.0e-7 with six products, 2.0e-7 with eight,
+// which cost 4-20 % more).  Two sequences of 8 images, 96 text rows, d = 128:
+// both passes 150 + 149 -> 69 + 65 us.
 template <>
 struct Mma<float> {
   static constexpr int E = 8;
@@ -442,8 +447,11 @@ struct P1Args {
 //
 // SMALL (fp32 inputs, grids of less than one block per CU): each tile's products
 // and then its masked sums, in a rolled loop.  A block runs a handful of tiles
-// there and is bound by latency, the fetch of its own code included: 11 KB of
-// code instead of 42, one sequence of 2 x 64 tokens, d = 64: 11.6 -> 8.1 us.
+// there and is bound by latency, the fetch of its own code included: 12 KB of
+// code instead of 52 at d = 64, 15 instead of 30 at d = 128.  The layer of one
+// sequence of 2 x 64 tokens (6 blocks) 23.9 -> 23.3 us at d = 64, 27.0 -> 26.2 at
+// d = 128; of 4 x 729 (184 blocks) 35.3 -> 35.0 and the same; row LSE of 256
+// blocks of 256 keys 14.0 -> 16.1 and 20.6 -> 22.2, which keep the unrolled form.
 // The bf16 kernel's unrolled tiles hide more than they cost: with this form 4 x
 // 729 tokens took 9.0 -> 9.9 us, two sequences of 8 images 20.2 -> 25.5.
 template <typename T, int D, int NT, bool SMALL>

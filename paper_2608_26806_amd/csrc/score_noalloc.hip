@@ -1,7 +1,7 @@
 // avtp_score_noalloc: avtp_score for callers that cannot allocate device
 // memory (code under HIP graph capture, tight serving loops, harnesses that
 // forbid hipMalloc).  The score passes' scratch (pass-1 partials, the row LSE
-// in both units, the pass-2 column-sum planes) lives in one file-scope device
+// in log2 units, the pass-2 column-sum planes) lives in one file-scope device
 // array of AVTP_NOALLOC_MAX_WORKSPACE bytes instead of a caller workspace.
 //
 // Each GPU holds its own copy of the array at its own address.  The address
