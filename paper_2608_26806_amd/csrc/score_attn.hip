@@ -1470,17 +1470,18 @@ AttnPlan attn_plan(const DevLayout &L, int Hq, int Hkv, int d, int dtype) {
   auto key_blocks = [&](int nt) { return (L.max_seqlen + 4 * nt * 32 - 1) / (4 * nt * 32); };
   auto blocks2 = [&](int nt) { return (long long)L.B * Hkv * key_blocks(nt); };
   // bf16 at d = 64 has half the work per tile and room for more blocks per CU:
-  // below 512 blocks of four tiles, two tiles only where they give 512 blocks,
-  // of more than one stage or with no fewer key tiles than one would take, else
-  // one, and the rows are split further (below).
+  // below 512 blocks of four tiles, two tiles only where they give 512 blocks, of
+  // more than one stage or where one tile would not save an eighth of the padded
+  // keys, else one, and the rows are split further (below).
   // Score with a given LSE, four tiles and their splits -> two and one by the
-  // rule above -> this: 8 x 8 images of 512 tokens, 14/2 heads, 19.3 -> 21.9 ->
-  // 18.5 us; 30 x 3 of 100, 16/16 heads, 13.8 -> 14.9 -> 13.3; 2 x 16 of 512,
-  // 28/4 heads, 42.3 -> 46.9 -> 39.0; 3 x 6 of 300, 14/2 heads, 14.8 -> 11.1 ->
-  // 11.1.
+  // rule above -> this: 8 x 8 images of 512 tokens, 14/2 heads, 19.4 -> 22.1 ->
+  // 17.8 us; 30 x 3 of 100, 16/16 heads (three blocks of one tile where two of
+  // two), 13.8 -> 14.8 -> 12.9; 2 x 16 of 512, 28/4 heads, 42.1 -> 46.7 -> 36.1;
+  // 3 x 6 of 300, 14/2 heads, 14.9 -> 11.2 -> 10.8.  8 of 1,024, two rows, 16/16
+  // heads: 14.7 -> 12.4 with two tiles, 13.0 with one.
   const bool wide64 = nkt2 == 4;
   if (wide64) {
-    const bool two = blocks2(2) >= 512 && (P.rows_max > kStage || blocks2(1) >= 2 * blocks2(2));
+    const bool two = blocks2(2) >= 512 && (P.rows_max > kStage || 8 * blocks2(1) > 7 * 2 * blocks2(2));
     if (blocks2(4) < 512) nkt2 = two ? 2 : 1;
   } else {
     if (nkt2 > 2 && blocks2(nkt2) < 512) nkt2 = 2;
@@ -1513,7 +1514,7 @@ AttnPlan attn_plan(const DevLayout &L, int Hq, int Hkv, int d, int dtype) {
     // The narrower blocks at d = 64: for 768 blocks (1,024: 4 x 4 images of 729
     // tokens, 32/8 heads, 14.5 -> 16.4 us) of at least two stages (of one: 2 x 9
     // of 775, 286 rows, 12/12 heads, 23.2 -> 27.1 us), and long rows every 512 up
-    // to 2,048 blocks (3 x 16 of 1,024, 512 text rows, 14/2 heads: 111 -> 92 us),
+    // to 2,048 blocks (3 x 16 of 1,024, 512 text rows, 14/2 heads: 110 -> 80 us),
     // whose column sums take no more room than those of 512 blocks of four tiles.
     if (wide64 && nkt2 < 4 && base2 >= 256) {
       const long long stages = (P.rows_max + kStage - 1) / kStage;
