@@ -131,6 +131,27 @@ def test_a_query_that_is_not_finite(d, value):
 
 
 @pytest.mark.parametrize("d", [64, 128])
+def test_a_key_that_is_not_a_number(d):
+    """Every text row after it sees it, so the tokens of its sequence that those
+    rows see score NaN; the other sequence is as the oracle has it."""
+    need_gpu()
+    say(f"fp32 scores, a key of NaN, d={d}")
+    lay, q, k = _draw((d, 4, 2, [[90, 150], [70]], 2, 20), 8)
+    k_bad = k.copy()
+    k_bad[int(lay.img_start[0]) + 33, 0, 5] = np.nan
+    dl = A.DeviceLayout(lay)
+    status = torch.zeros(lay.B, dtype=torch.int32, device="cuda")
+    s, _ = A.score_attn(dl, torch.from_numpy(q).cuda(), torch.from_numpy(k_bad).cuda(), d ** -0.5,
+                        status=status)
+    s_o, _, _, _ = O.attn_scores(lay, q, k, 4, 2, d ** -0.5, "fp32")
+    s, vis = s.cpu().numpy(), lay.visual_mask()
+    first = np.arange(lay.N_tok) < int(lay.cu_seqlens[1])
+    assert np.isnan(s[vis & first]).all()
+    assert [x & 1 for x in status.tolist()] == [1, 0]
+    np.testing.assert_allclose(s[vis & ~first], s_o[vis & ~first], rtol=TOL["fp32"])
+
+
+@pytest.mark.parametrize("d", [64, 128])
 def test_partly_filled_row_tiles_cost_no_more_than_full_ones(d):
     """40 query rows per key head (a full row tile and one of 8 rows) against 64
     (two full tiles) over the same keys: the same tiles, so not slower.  The
